@@ -554,144 +554,174 @@ __device__ __forceinline__ void leg_mean_v1(double t0, double t1, int s, double 
     }
 }
 
+// The mean along a leg that stays in cell c0: the same vector, from one piece
+// (entries 0 and P + 1 are zero).
+template <int P>
+__device__ __forceinline__ void leg_mean_cell(double t0, double t1, double (&lb)[P + 2]) {
+    double avg[P];
+    piece_means<P - 1>(t0, t1, avg);   // symmetric in its two ends
+    lb[0] = 0.0;
+    lb[P + 1] = 0.0;
+#pragma unroll
+    for (int k = 1; k <= P; ++k) lb[k] = avg[P - k];
+}
+
 // 1 / |s| for a leg of s cells, with |s| raised to a tiny normal floor: a leg
 // that crosses a grid line is longer than that unless it starts within the
 // floor of the line, where the split of its (vanishing) length does not matter.
 __device__ __forceinline__ double leg_rcp(double s) { return frcp(fmax(fabs(s), 1.0e-290)); }
 
-// Path integrals of the V1 basis on one piece of the straight step (between two
-// grid-line crossings, inside cell (k1, k2)), both components, by the P-point
-// Gauss-Legendre rule in the piece's own frame: W1[u][v] is the integral over
-// the piece (parameter length len) of N^{P-1}_{k1-(P-1)+u}(x1) N^P_{k2-P+v}(x2),
-// W2[u][v] that of N^P_{k1-P+u}(x1) N^{P-1}_{k2-(P-1)+v}(x2).
-template <int P>
-__device__ __forceinline__ void piece_integrals(double x1, double x2, double s1, double s2, int k1, int k2,
-                                                double sa, double len, double (&W1)[P][P + 1],
-                                                double (&W2)[P + 1][P]) {
+// Path integrals of one V1 component on one piece of the straight step (between
+// two grid-line crossings), by the P-point Gauss-Legendre rule in the frame of the
+// piece's cell: W[u][v] is the integral over the piece (parameter from sa, length
+// len) of N^{DA}_{-DA+u}(x1) N^{DB}_{-DB+v}(x2), with (DA, DB) = (P-1, P) or
+// (P, P-1) and the step starting at (t1, t2) with slope (s1, s2).  The two
+// components use disjoint basis values, so taking them in turn costs nothing and
+// halves the registers the integrals hold.
+template <int P, int DA, int DB>
+__device__ __forceinline__ void piece_integrals(double t1, double t2, double s1, double s2, double sa, double len,
+                                                double (&W)[DA + 1][DB + 1]) {
 #pragma unroll
-    for (int u = 0; u < P; ++u)
+    for (int u = 0; u <= DA; ++u)
 #pragma unroll
-        for (int v = 0; v < P + 1; ++v) { W1[u][v] = 0.0; W2[v][u] = 0.0; }
+        for (int v = 0; v <= DB; ++v) W[u][v] = 0.0;
 #pragma unroll
     for (int q = 0; q < P; ++q) {
         const double s = sa + len * GL<P>::x[q];
         const double g = len * GL<P>::w[q];
-        const double t1 = x1 + s * s1 - k1, t2 = x2 + s * s2 - k2;
-        double b0x[P + 1], b1x[P], b0y[P + 1], b1y[P];
-        basis_values<P>(t1, b0x);       // b0x[m]: N^P_{k1-m}
-        basis_values<P - 1>(t1, b1x);   // b1x[m]: N^{P-1}_{k1-m}
-        basis_values<P>(t2, b0y);
-        basis_values<P - 1>(t2, b1y);
+        double bx[DA + 1], by[DB + 1];
+        basis_values<DA>(t1 + s * s1, bx);   // bx[m]: N^{DA}_{-m}
+        basis_values<DB>(t2 + s * s2, by);
 #pragma unroll
-        for (int u = 0; u < P; ++u) {
-            const double gx = g * b1x[P - 1 - u], gy = g * b1y[P - 1 - u];
+        for (int u = 0; u <= DA; ++u) {
+            const double gx = g * bx[DA - u];
 #pragma unroll
-            for (int v = 0; v < P + 1; ++v) {
-                W1[u][v] += gx * b0y[P - v];
-                W2[v][u] += gy * b0x[P - v];
-            }
+            for (int v = 0; v <= DB; ++v) W[u][v] += gx * by[DB - v];
         }
     }
 }
 
-// The field patch of a tile in LDS (rows r-P-1 .. r+1, columns c0-P-1 .. c0+TW).
+// The field patch of a tile in LDS (rows r-P-1 .. r+1, columns c0-P-1 .. c0+TW),
+// rows PC apart for every tile width, so that offsets inside it are constants.
+template <int P>
 struct Patch {
+    static constexpr int PC = TWMAX + P + 2, PR = P + 3, SIZE = PR * PC;
     double *E1, *E2, *A, *G1, *G2, *J1, *J2, *Bz;
-    int PC, R0, C0, r;
+    int R0, C0, r;
 };
 
-// One particle's step geometry (cell units): start x, increment s, end y, the
-// start/end cells, the lower-left cell of the step and the path parameters lo <=
-// hi of its grid-line crossings (1 when there is none).
-struct Geo {
-    double x1, x2, q1, q2, D1, D2, s1, s2, y1, y2, lo, hi;
-    int ca2, cb1, cb2, mn1, mn2;
+// One particle's step (cell units): the start in its own cell (r, c2) as t in
+// [0, 1), the increment s (D in physical units) and the end u in that cell's
+// frame, the cell change e of the end point, and the momentum q.  A crossing
+// step also has the path parameters lo <= hi of its grid-line crossings (1 when
+// there is none).
+struct Step {
+    double t1, t2, s1, s2, u1, u2, D1, D2, q1, q2, lo, hi;
+    int c2, e1, e2;
 };
 
-__device__ __forceinline__ Geo geometry(const SweepArgs &a, double x1, double x2, double q1, double q2, double D1,
-                                        double D2, bool live, int r, int &flags) {
-    Geo g;
-    g.x1 = x1;
-    g.x2 = x2;
+__device__ __forceinline__ Step make_step(const SweepArgs &a, double x1, double x2, double q1, double q2, double D1,
+                                          double D2, int r) {
+    Step g;
+    g.c2 = (int)x2;
+    g.t1 = x1 - r;
+    g.t2 = x2 - g.c2;
+    g.s1 = D1 * a.inv_dx1;
+    g.s2 = D2 * a.inv_dx2;
+    g.u1 = (x1 + g.s1) - r;
+    g.u2 = (x2 + g.s2) - g.c2;
+    g.D1 = D1;
+    g.D2 = D2;
     g.q1 = q1;
     g.q2 = q2;
-    g.D1 = live ? D1 : 0.0;
-    g.D2 = live ? D2 : 0.0;
-    g.s1 = g.D1 * a.inv_dx1;
-    g.s2 = g.D2 * a.inv_dx2;
-    g.y1 = g.x1 + g.s1;
-    g.y2 = g.x2 + g.s2;
-    const int ca1 = r;
-    g.ca2 = (int)g.x2;
-    g.cb1 = (int)floor(g.y1);
-    g.cb2 = (int)floor(g.y2);
-    if (g.cb1 < ca1 - 1 || g.cb1 > ca1 + 1 || g.cb2 < g.ca2 - 1 || g.cb2 > g.ca2 + 1 || !isfinite(g.s1 + g.s2)) {
-        if (live) flags |= isfinite(g.s1 + g.s2) ? FLAG_CFL : FLAG_NONFINITE;
-        g.cb1 = ca1;
-        g.cb2 = g.ca2;
-    }
-    g.mn1 = min(ca1, g.cb1);
-    g.mn2 = min(g.ca2, g.cb2);
-    const double bA = g.cb1 != ca1 ? ((double)max(ca1, g.cb1) - g.x1) * copysign(leg_rcp(g.s1), g.s1) : 1.0;
-    const double bB = g.cb2 != g.ca2 ? ((double)max(g.ca2, g.cb2) - g.x2) * copysign(leg_rcp(g.s2), g.s2) : 1.0;
-    g.lo = fmin(bA, bB);
-    g.hi = fmax(bA, bB);
+    g.e1 = g.e2 = 0;
+    g.lo = g.hi = 1.0;
     return g;
 }
 
-// Pieces first..last of the path (0: [0, lo], 1: [lo, hi], 2: [hi, 1]): the mean
-// field is accumulated into E1, E2 and w d times the path integrals of the V1 basis
-// are added to the current patch.  Pieces no lane of the wave needs are skipped.
-template <int P>
-__device__ __forceinline__ void pieces(const Geo &g, bool live, int first, int last, const Patch &t, double w,
-                                       double &E1, double &E2) {
-    const double j1 = w * g.D1, j2 = w * g.D2;
-    const int PC = t.PC;
-#pragma unroll 1
-    for (int piece = first; piece <= last; ++piece) {
-        const double sa = piece == 0 ? 0.0 : (piece == 1 ? g.lo : g.hi);
-        const double sb = piece == 0 ? g.lo : (piece == 1 ? g.hi : 1.0);
-        const double len = live ? sb - sa : 0.0;
-        if (!__builtin_amdgcn_ballot_w64(len > 0.0)) continue;
-        const double sm = 0.5 * (sa + sb);
-        const int k1 = min(max((int)floor(g.x1 + sm * g.s1), g.mn1), g.mn1 + 1);
-        const int k2 = min(max((int)floor(g.x2 + sm * g.s2), g.mn2), g.mn2 + 1);
-        double W1[P][P + 1], W2[P + 1][P];
-        piece_integrals<P>(g.x1, g.x2, g.s1, g.s2, k1, k2, sa, len, W1, W2);
-        const int o1 = (k1 - (P - 1) - t.R0) * PC + k2 - P - t.C0;   // W1[0][0] in the patch
-        const int o2 = (k1 - P - t.R0) * PC + k2 - (P - 1) - t.C0;   // W2[0][0]
+// Does the step end in its own cell (false for a non-finite one)?
+__device__ __forceinline__ bool stays(const Step &g) {
+    return g.u1 >= 0.0 && g.u1 < 1.0 && g.u2 >= 0.0 && g.u2 < 1.0;
+}
+
+// Cell change and crossing parameters of a step that leaves its cell.
+__device__ __forceinline__ void cross_step(Step &g, bool live, int &flags) {
+    const double f1 = floor(g.u1), f2 = floor(g.u2);
+    if (!(fabs(f1) <= 1.0 && fabs(f2) <= 1.0)) {   // a cell or more, or not finite
+        if (live) flags |= isfinite(g.s1 + g.s2) ? FLAG_CFL : FLAG_NONFINITE;
+    } else {
+        g.e1 = (int)f1;
+        g.e2 = (int)f2;
+    }
+    const double bA = g.e1 ? ((g.e1 > 0 ? 1.0 : 0.0) - g.t1) * copysign(leg_rcp(g.s1), g.s1) : 1.0;
+    const double bB = g.e2 ? ((g.e2 > 0 ? 1.0 : 0.0) - g.t2) * copysign(leg_rcp(g.s2), g.s2) : 1.0;
+    g.lo = fmin(bA, bB);
+    g.hi = fmax(bA, bB);
+}
+
+// One piece of the path inside the cell (k1, k2) relative to the start cell, from
+// parameter sa over length len, for the component of degrees (DA, DB) with the
+// patches F (mean field) and J (current): the mean field is accumulated into E
+// and jw times the path integrals of the V1 basis are added to the current.
+template <int P, int DA, int DB>
+__device__ __forceinline__ void piece_of(const Step &g, bool live, double sa, double len, int k1, int k2,
+                                         const Patch<P> &t, const double *F, double *J, double jw, double &E) {
+    constexpr int PC = Patch<P>::PC;
+    double W[DA + 1][DB + 1];
+    piece_integrals<P, DA, DB>(g.t1 - k1, g.t2 - k2, g.s1, g.s2, sa, len, W);
+    const int o = (P + 1 - DA + k1) * PC + g.c2 - t.C0 + k2 - DB;   // W[0][0] in the patch
 #pragma unroll
-        for (int u = 0; u < P; ++u)
+    for (int u = 0; u <= DA; ++u)
 #pragma unroll
-            for (int v = 0; v < P + 1; ++v) {
-                E1 += W1[u][v] * t.E1[o1 + u * PC + v];
-                E2 += W2[v][u] * t.E2[o2 + v * PC + u];
-            }
-        if (len > 0.0) {
+        for (int v = 0; v <= DB; ++v) E += W[u][v] * F[o + u * PC + v];
+    asm volatile("" : "+v"(E));   // summed before the deposit, not at the push (see legs_of)
+    if (live) {
 #pragma unroll
-            for (int u = 0; u < P; ++u)
+        for (int u = 0; u <= DA; ++u)
 #pragma unroll
-                for (int v = 0; v < P + 1; ++v) {
-                    atomicAdd(&t.J1[o1 + u * PC + v], j1 * W1[u][v]);
-                    atomicAdd(&t.J2[o2 + v * PC + u], j2 * W2[v][u]);
-                }
-        }
+            for (int v = 0; v <= DB; ++v) atomicAdd(&J[o + u * PC + v], jw * W[u][v]);
     }
 }
 
-// A_z at a start point x (x1 in the tile's row) from the patch.
+// Both components of one piece.
 template <int P>
-__device__ __forceinline__ double start_A(const Patch &t, double x1, double x2) {
-    const int c2 = (int)x2;
+__device__ __forceinline__ void piece(const Step &g, bool live, double sa, double len, int k1, int k2,
+                                      const Patch<P> &t, double w, double &E1, double &E2) {
+    piece_of<P, P - 1, P>(g, live, sa, len, k1, k2, t, t.E1, t.J1, w * g.D1, E1);
+    __builtin_amdgcn_sched_barrier(0);   // the second component's integrals reuse the first one's registers
+    piece_of<P, P, P - 1>(g, live, sa, len, k1, k2, t, t.E2, t.J2, w * g.D2, E2);
+}
+
+// The pieces of a crossing path ([0, lo], [lo, hi], [hi, 1]); those no lane of the
+// wave needs are skipped.
+template <int P>
+__device__ __forceinline__ void pieces(const Step &g, bool live, const Patch<P> &t, double w, double &E1, double &E2) {
+    const int n1 = min(g.e1, 0), n2 = min(g.e2, 0);
+#pragma unroll 1
+    for (int q = 0; q < 3; ++q) {
+        const double sa = q == 0 ? 0.0 : (q == 1 ? g.lo : g.hi);
+        const double sb = q == 0 ? g.lo : (q == 1 ? g.hi : 1.0);
+        const double len = live ? sb - sa : 0.0;
+        if (!__builtin_amdgcn_ballot_w64(len > 0.0)) continue;
+        const double sm = 0.5 * (sa + sb);
+        const int k1 = min(max((int)floor(g.t1 + sm * g.s1), n1), n1 + 1);
+        const int k2 = min(max((int)floor(g.t2 + sm * g.s2), n2), n2 + 1);
+        piece<P>(g, len > 0.0, sa, len, k1, k2, t, w, E1, E2);
+    }
+}
+
+// A_z at a start point (t1, t2) of the tile's row, cell column c2, from the patch.
+template <int P>
+__device__ __forceinline__ double start_A(const Patch<P> &t, double t1, double t2, int c2) {
     double b1[P + 1], b2[P + 1];
-    basis_values<P>(x1 - t.r, b1);
-    basis_values<P>(x2 - c2, b2);
+    basis_values<P>(t1, b1);
+    basis_values<P>(t2, b2);
     double A = 0.0;
 #pragma unroll
     for (int m1 = 0; m1 <= P; ++m1) {
         double ta = 0.0;
 #pragma unroll
-        for (int m2 = 0; m2 <= P; ++m2) ta += b2[m2] * t.A[(t.r - m1 - t.R0) * t.PC + c2 - m2 - t.C0];
+        for (int m2 = 0; m2 <= P; ++m2) ta += b2[m2] * t.A[(P + 1 - m1) * Patch<P>::PC + c2 - m2 - t.C0];
         A += b1[m1] * ta;
     }
     return A;
@@ -702,59 +732,75 @@ __device__ __forceinline__ double gamma_of(double q1, double q2, double A) {
     return fsqrt(1.0 + q1 * q1 + q2 * q2 + A * A);
 }
 
-// A_z at the end point, the means of dA_z/dx2 along the vertical leg (at x1^n) and
-// of dA_z/dx1 along the horizontal leg (at x2^{n+1}), the push of the Subsystem I
-// scheme, and the stores of particle i.  Aa = A_z(x^n) and gA = gamma(x^n, p^n)
-// are fixed over the iteration.
-template <int P, bool SPIN>
-__device__ __forceinline__ void finish(const Geo &g, bool live, int i, double E1, double E2, double Aa, double gA,
-                                       const Patch &t, const SweepArgs &a, double &rmax, int &flags) {
-    const int PC = t.PC, R0 = t.R0, C0 = t.C0, ca1 = t.r, ca2 = g.ca2, cb1 = g.cb1, cb2 = g.cb2;
-    double ba1[P + 1], bb1[P + 1], bb2[P + 1];
-    basis_values<P>(g.x1 - ca1, ba1);
-    basis_values<P>(g.y1 - cb1, bb1);
-    basis_values<P>(g.y2 - cb2, bb2);
-    double Ab = 0.0;
-#pragma unroll
-    for (int m1 = 0; m1 <= P; ++m1) {
-        double tb = 0.0;
-#pragma unroll
-        for (int m2 = 0; m2 <= P; ++m2) tb += bb2[m2] * t.A[(cb1 - m1 - R0) * PC + cb2 - m2 - C0];
-        Ab += bb1[m1] * tb;
+// What the push needs from the two legs of a step: the means of dA_z/dx2 along
+// the vertical leg (Dv, at x1^n) and of dA_z/dx1 along the horizontal leg (Dh, at
+// x2^{n+1}), and the spin force over hbar (F1, F2).
+struct Legs {
+    double Dv, Dh, F1, F2;
+};
+
+// All patch reads of the push: taken before the path integrals deposit, because
+// LDS operations of a wave complete in order and reads behind the deposit's
+// atomics would wait for them.  CROSS: the legs may enter a neighbour cell
+// (otherwise they stay, and P of their P + 2 weights are nonzero).
+template <int P, bool SPIN, bool CROSS>
+__device__ __forceinline__ Legs legs_of(const Step &g, int i, const Patch<P> &t, const SweepArgs &a) {
+    constexpr int PC = Patch<P>::PC, R = P + 1;            // R: the tile's row in the patch
+    constexpr int KA = CROSS ? 0 : 1, KB = CROSS ? P + 1 : P;   // leg entries that can be nonzero
+    const int c = g.c2 - t.C0;                             // column of the start cell in the patch
+    const int cb = CROSS ? c + g.e2 : c;                   // of the end cell
+    double ba1[P + 1], bb2[P + 1];
+    basis_values<P>(g.t1, ba1);
+    basis_values<P>(CROSS ? g.u2 - g.e2 : g.u2, bb2);
+    double rl2 = 0.0, rl1 = 0.0, lm2[P + 2], lm1[P + 2];   // index (start cell) - P + k
+    if constexpr (CROSS) {
+        rl2 = leg_rcp(g.s2);
+        rl1 = leg_rcp(g.s1);
+        leg_mean_v1<P>(g.t2, g.u2, g.e2, rl2, lm2);
+        leg_mean_v1<P>(g.t1, g.u1, g.e1, rl1, lm1);
+    } else {
+        leg_mean_cell<P>(g.t2, g.u2, lm2);
+        leg_mean_cell<P>(g.t1, g.u1, lm1);
     }
-    const double rl2 = leg_rcp(g.s2), rl1 = leg_rcp(g.s1);
-    double lm2[P + 2], lm1[P + 2];
-    leg_mean_v1<P>(g.x2 - ca2, g.y2 - ca2, cb2 - ca2, rl2, lm2);   // indices ca2 - P + k
-    leg_mean_v1<P>(g.x1 - ca1, g.y1 - ca1, cb1 - ca1, rl1, lm1);   // indices ca1 - P + k
     double Dv = 0.0, Dh = 0.0;
 #pragma unroll
     for (int m1 = 0; m1 <= P; ++m1) {
         double s = 0.0;
 #pragma unroll
-        for (int k = 0; k < P + 2; ++k) s += lm2[k] * t.G2[(ca1 - m1 - R0) * PC + ca2 - P + k - C0];
+        for (int k = KA; k <= KB; ++k) s += lm2[k] * t.G2[(R - m1) * PC + c - P + k];
         Dv += ba1[m1] * s;
     }
 #pragma unroll
-    for (int k = 0; k < P + 2; ++k) {
+    for (int k = KA; k <= KB; ++k) {
         double s = 0.0;
 #pragma unroll
-        for (int m2 = 0; m2 <= P; ++m2) s += bb2[m2] * t.G1[(ca1 - P + k - R0) * PC + cb2 - m2 - C0];
+        for (int m2 = 0; m2 <= P; ++m2) s += bb2[m2] * t.G1[(R - P + k) * PC + cb - m2];
         Dh += lm1[k] * s;
     }
+    // formed here: the compiler would otherwise sink the arithmetic to the push and
+    // keep every patch value read alive across the path integrals
+    asm volatile("" : "+v"(Dv), "+v"(Dh));
     double F1 = 0.0, F2 = 0.0;   // spin force / hbar
     if constexpr (SPIN) {
+        __builtin_amdgcn_sched_barrier(0);
         // Means along the same two legs of the derivatives of dA_z/dx2 (coefficients
         // G2 = (G a)_2, degrees (P, P-1)), dA_z/dx1 (G1, (P-1, P)) and B_z ((P-1, P-1)):
         // each derivative's coefficients are backward differences of the field's.
-        double lq2[P + 1], lq1[P + 1], bm1[P], bmb2[P];
-        leg_mean_v1<P - 1>(g.x2 - ca2, g.y2 - ca2, cb2 - ca2, rl2, lq2);   // degree P-2, indices ca2 - P + 1 + k
-        leg_mean_v1<P - 1>(g.x1 - ca1, g.y1 - ca1, cb1 - ca1, rl1, lq1);   // degree P-2, indices ca1 - P + 1 + k
-        basis_values<P - 1>(g.x1 - ca1, bm1);
-        basis_values<P - 1>(g.y2 - cb2, bmb2);
+        double lq2[P + 1], lq1[P + 1], bm1[P], bmb2[P];   // legs of degree P-2, index (start cell) - P + 1 + k
+        if constexpr (CROSS) {
+            leg_mean_v1<P - 1>(g.t2, g.u2, g.e2, rl2, lq2);
+            leg_mean_v1<P - 1>(g.t1, g.u1, g.e1, rl1, lq1);
+        } else {
+            leg_mean_cell<P - 1>(g.t2, g.u2, lq2);
+            leg_mean_cell<P - 1>(g.t1, g.u1, lq1);
+        }
+        basis_values<P - 1>(g.t1, bm1);
+        basis_values<P - 1>(CROSS ? g.u2 - g.e2 : g.u2, bmb2);
         const double i1 = a.inv_dx1, i2 = a.inv_dx2;
         // Summation by parts: sum_k m_k (F_k - F_{k-1}) = sum_j F_j (m_j - m_{j+1}), so
-        // every patch value is read once, with difference weights formed once.
-        // x2 leg at x1^n: columns ca2 - P - 1 + j, j = 0..P+2.
+        // every patch value is read once, with difference weights formed once.  Entry j
+        // of a weight vector belongs to index (start cell) - P - 1 + j; those of lm are
+        // nonzero for j in [KA, KB + 1], those of lq for j in [KA + 1, KB + 1].
         double wa[P + 3], wb[P + 3];   // weights of lm2 (degree P-1) and lq2 (degree P-2)
 #pragma unroll
         for (int j = 0; j <= P + 2; ++j) {
@@ -766,13 +812,13 @@ __device__ __forceinline__ void finish(const Geo &g, bool live, int i, double E1
         double Sy2 = 0.0, Sx2 = 0.0, Sb2 = 0.0;
 #pragma unroll
         for (int m1 = 0; m1 <= P; ++m1) {
-            const int row = (ca1 - m1 - R0) * PC - C0 + ca2 - P - 1;
+            const int row = (R - m1) * PC + c - P - 1;
             double ty = 0.0, tx = 0.0, tb = 0.0;
 #pragma unroll
-            for (int j = 0; j <= P + 2; ++j) {
-                if (j >= 1) ty += wb[j] * t.G2[row + j];
+            for (int j = KA; j <= KB + 1; ++j) {
+                if (j > KA) ty += wb[j] * t.G2[row + j];
                 tx += wa[j] * t.G1[row + j];
-                if (j >= 1) tb += wb[j] * t.Bz[row + j];
+                if (j > KA) tb += wb[j] * t.Bz[row + j];
             }
             Sy2 += ba1[m1] * ty;
             if (m1 < P) {
@@ -780,41 +826,58 @@ __device__ __forceinline__ void finish(const Geo &g, bool live, int i, double E1
                 Sb2 += bm1[m1] * tb;
             }
         }
-        // x1 leg at x2^{n+1}: rows ca1 - P - 1 + j, j = 0..P+2; per row the x2 sums first.
+        asm volatile("" : "+v"(Sy2), "+v"(Sx2), "+v"(Sb2));
+        __builtin_amdgcn_sched_barrier(0);
+        // x1 leg at x2^{n+1}: per row the x2 sums first.
         double Sy1 = 0.0, Sx1 = 0.0, Sb1 = 0.0;
 #pragma unroll
-        for (int j = 0; j <= P + 2; ++j) {
+        for (int j = KA; j <= KB + 1; ++j) {
             const double m0 = j >= 1 ? lm1[j - 1] : 0.0, m1 = j <= P + 1 ? lm1[j] : 0.0;
             const double q0 = j >= 2 ? lq1[j - 2] : 0.0, q1 = (j >= 1 && j <= P + 1) ? lq1[j - 1] : 0.0;
-            const int row = (ca1 - P - 1 + j - R0) * PC - C0;
+            const int row = (R - P - 1 + j) * PC;
             double ty = 0.0, tx = 0.0, tb = 0.0;
 #pragma unroll
             for (int m2 = 0; m2 <= P; ++m2) {
-                const int c = row + cb2 - m2;
-                tx += bb2[m2] * t.G1[c];
+                const int k = row + cb - m2;
+                if (j > KA) tx += bb2[m2] * t.G1[k];
                 if (m2 < P) {
-                    ty += bmb2[m2] * t.G2[c];
-                    tb += bmb2[m2] * t.Bz[c];
+                    ty += bmb2[m2] * t.G2[k];
+                    if (j > KA) tb += bmb2[m2] * t.Bz[k];
                 }
             }
             Sy1 += (m0 - m1) * ty;
-            Sx1 += (q0 - q1) * tx;
-            Sb1 += (q0 - q1) * tb;
+            if (j > KA) {
+                Sx1 += (q0 - q1) * tx;
+                Sb1 += (q0 - q1) * tb;
+            }
         }
         const double sx = a.sx[i], sy = a.sy[i], sz = a.sz[i];
         F1 = (sx * Sy1 - sy * Sx1 + sz * Sb1) * i1;
         F2 = (sx * Sy2 - sy * Sx2 + sz * Sb2) * i2;
     }
+    if constexpr (SPIN) asm volatile("" : "+v"(F1), "+v"(F2));
+    return Legs{Dv, Dh, F1, F2};
+}
+
+// The push of the Subsystem I scheme and the stores of particle i.  Aa = A_z(x^n)
+// and gA = gamma(x^n, p^n) are fixed over the iteration; A_z at the end point is Aa
+// plus the two legs' increments (the leg means are exact divided differences): 2
+// operations instead of a gather, and (Aa + Ab)(D1 Dh + D2 Dv) = Ab^2 - Aa^2 then
+// holds to rounding.
+template <bool SPIN>
+__device__ __forceinline__ void push(const Step &g, bool live, int i, double E1, double E2, double Aa, double gA,
+                                     const Legs &l, const SweepArgs &a, double &rmax, int &flags) {
+    const double Ab = Aa + (g.D1 * l.Dh + g.D2 * l.Dv);
     const double q1 = g.q1, q2 = g.q2;
     const double gB = gamma_of(q1, q2, Ab);
     const double f = -(Aa + Ab) * frcp(gA + gB);
     double n1, n2;
     if constexpr (SPIN) {
-        n1 = q1 + a.dt * (E1 + f * Dh - a.hbar * F1);
-        n2 = q2 + a.dt * (E2 + f * Dv - a.hbar * F2);
+        n1 = q1 + a.dt * (E1 + f * l.Dh - a.hbar * l.F1);
+        n2 = q2 + a.dt * (E2 + f * l.Dv - a.hbar * l.F2);
     } else {
-        n1 = q1 + a.dt * (E1 + f * Dh);
-        n2 = q2 + a.dt * (E2 + f * Dv);
+        n1 = q1 + a.dt * (E1 + f * l.Dh);
+        n2 = q2 + a.dt * (E2 + f * l.Dv);
     }
     const double gC = gamma_of(n1, n2, Ab);
     const double sc = a.dt * frcp(gB + gC);
@@ -829,37 +892,47 @@ __device__ __forceinline__ void finish(const Geo &g, bool live, int i, double E1
     }
 }
 
-// One sweep over a tile.  Every particle integrates the first piece of its path
-// inline; a step that crosses a grid line needs one or two more pieces, and such
-// particles (about one in ten) are parked, with their position, increment and
-// partial mean field, in a per-wave LDS queue and finished 64 at a time, so that
-// the waves do not run the extra pieces for lanes that have none (only the
-// momentum is read again).
-constexpr int QCAP = 2 * WAVE;
-constexpr int QV = 6;   // x1, x2, d1, d2, E1, E2
+// One sweep over a tile.  A step that stays in its cell (about nine in ten) is
+// done inline: one path piece in the cell's own frame, and leg means whose P
+// nonzero weights come from one piece.  A step that crosses a grid line has
+// two or three pieces and legs of two; the indices of such particles wait in a
+// per-wave LDS queue and are done with every term 64 at a time, so that the waves
+// do not run the extra terms for lanes that have none.  The re-sort stores the
+// particles expected to cross behind the others of their tile, so the rows here
+// are nearly all of one kind: the queue fills a row at once, whose lines are
+// still in cache when it is read again, and stores cover whole lines.
+//
+// Bound by HBM and by the latency of its dependent chains at two or three waves
+// per SIMD (registers); at 512 x 512 cells, 2^24 particles, degree 3: 96 B per
+// particle, about 560 vector and 72 LDS instructions per row of 64 (917 and 87
+// with the general terms run for every lane), 478 us per launch against 660 us
+// with crossing particles inline in any order and the general terms (events).
+// Taking the 24 LDS atomics out would give 50 us.  More waves do not help when
+// their registers spill: 629 us at four waves per SIMD (degree 3).
+constexpr int QCAP = 2 * WAVE;   // fewer than 64 wait when a row starts
 
 // FIRST (sweep 0): the increment is the explicit start d^(0) = dt p^n /
 // gamma(x^n, p^n), formed from A_z on the patch and stored with A_z(x^n) and
-// gamma(x^n, p^n), which the later sweeps read instead; that variant is held
-// to three waves per SIMD (168 VGPRs) at p = 3, like the others.  SPIN: the
-// spin force as well; held to three waves per SIMD for p <= 3 (a few registers
-// spilled) after the first sweep, two in it.
+// gamma(x^n, p^n), which the later sweeps read instead.
+//
+// Waves per SIMD: what the registers allow without spills.  With spin two at
+// degree 3 (199 registers): 191 us per launch at 256 x 256 cells and 2^22
+// particles, 243 us at three (168, 112 B per lane spilled).
 template <int P, bool FIRST, bool SPIN>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(!SPIN ? (FIRST && P == 3 ? 3 : 1)
-                                                                            : (P <= 3 ? (FIRST ? 2 : 3) : 1)))) void k2_sweep_I(
-    SweepArgs a) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(P <= 3 ? (SPIN ? 2 : 3) : 2))) void k2_sweep_I(SweepArgs a) {
     if (*a.gate) return;   // uniform over the grid
-    constexpr int PR = P + 3, PCM = TWMAX + P + 2, PS = PR * PCM;
+    using PT = Patch<P>;
+    constexpr int PS = PT::SIZE, PC = PT::PC;
     __shared__ double sE1[PS], sE2[PS], sA[PS], sG1[PS], sG2[PS], sJ1[PS], sJ2[PS], sBz[SPIN ? PS : 1];
     __shared__ int qI[BLOCK / WAVE][QCAP];
-    __shared__ double qV[BLOCK / WAVE][QV][QCAP];
     const int nseg = a.M2 / a.TW;
     const int tile = tile_of_block();
     const int r = tile / nseg, c0 = (tile - r * nseg) * a.TW;
-    const int PC = a.TW + P + 2;
-    const Patch t{sE1, sE2, sA, sG1, sG2, sJ1, sJ2, sBz, PC, r - P - 1, c0 - P - 1, r};
-    for (int k = threadIdx.x; k < PR * PC; k += blockDim.x) {
+    const int width = a.TW + P + 2;   // columns of the patch in use
+    const PT t{sE1, sE2, sA, sG1, sG2, sJ1, sJ2, sBz, r - P - 1, c0 - P - 1, r};
+    for (int k = threadIdx.x; k < PS; k += blockDim.x) {
         const int i = k / PC, j = k - i * PC;
+        if (j >= width) continue;
         const int g = wrapi(t.R0 + i, a.M1) * a.M2 + wrapi(t.C0 + j, a.M2);
         sE1[k] = a.eb1[g];
         sE2[k] = a.eb2[g];
@@ -870,84 +943,115 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(!SPIN ? (
         sJ2[k] = 0.0;
         if constexpr (SPIN) sBz[k] = a.bz[g];
     }
-    __syncthreads();
     const int begin = a.start[tile], end = a.start[tile + 1];
     const int wid = threadIdx.x / WAVE, lane = lane_id();
     int *const qi = qI[wid];
-    double(*const qv)[QCAP] = qV[wid];
     double rmax = 0.0;
     int flags = 0;
-    int head = 0, tail = 0;   // queue of this wave (uniform)
-    // finish the n <= 64 oldest queued particles, one per lane
-    auto drain = [&](int n) {
-        const bool valid = lane < n;
-        const int slot = (head + lane) & (QCAP - 1);
-        double v[QV];
-#pragma unroll
-        for (int q = 0; q < QV; ++q) v[q] = valid ? qv[q][slot] : 0.0;
-        const int i = valid ? qi[slot] : begin;
-        if (!valid) v[0] = (double)r, v[1] = (double)c0;   // any point of the tile
-        double E1 = v[4], E2 = v[5];
-        const double q1 = a.p1[i], q2 = a.p2[i];
-        const Geo g = geometry(a, v[0], v[1], q1, q2, v[2], v[3], valid, r, flags);
-        pieces<P>(g, valid, 1, 2, t, a.w, E1, E2);
-        const double An = start_A<P>(t, v[0], v[1]);   // formed again rather than queued
-        finish<P, SPIN>(g, valid, i, E1, E2, An, gamma_of(q1, q2, An), t, a, rmax, flags);
-        head += n;
-    };
-    const int nw = blockDim.x / WAVE, passes = (end - begin + WAVE - 1) / WAVE;   // none for an empty tile
-    for (int jr = wid; jr < passes; jr += nw) {
-        const int i = begin + jr * WAVE + lane;
-        const bool live = i < end;
-        const int ii = live ? i : begin;
-        const double x1 = a.xi1[ii], x2 = a.xi2[ii], q1 = a.p1[ii], q2 = a.p2[ii];
-        double D1, D2, An, gn;
-        if constexpr (FIRST) {
-            An = start_A<P>(t, x1, x2);
-            gn = gamma_of(q1, q2, An);
-            const double sc = a.dt * frcp(gn);
-            D1 = q1 * sc;
-            D2 = q2 * sc;
-            if (live) {
-                a.d1[i] = D1;
-                a.d2[i] = D2;
-                a.azn[i] = An;
-                a.gamn[i] = gn;
-            }
-        } else {
-            D1 = a.d1[ii];
-            D2 = a.d2[ii];
-            An = a.azn[ii];
-            gn = a.gamn[ii];
-        }
-        const Geo g = geometry(a, x1, x2, q1, q2, D1, D2, live, r, flags);
-        double E1 = 0.0, E2 = 0.0;
-        pieces<P>(g, live, 0, 0, t, a.w, E1, E2);
-        const bool cross = live && g.lo < 1.0;
-        const unsigned long long cm = __builtin_amdgcn_ballot_w64(cross);
-        if (cross) {
-            const int slot = (tail + rank_in(cm)) & (QCAP - 1);
-            qi[slot] = i;
-            qv[0][slot] = x1;
-            qv[1][slot] = x2;
-            qv[2][slot] = D1;
-            qv[3][slot] = D2;
-            qv[4][slot] = E1;
-            qv[5][slot] = E2;
-        }
-        tail += __builtin_popcountll(cm);
-        if (live && !cross) finish<P, SPIN>(g, live, i, E1, E2, An, gn, t, a, rmax, flags);
+    int qn = 0;   // particles waiting in this wave's queue (uniform)
+    auto wave_fence = [] {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (tail - head >= WAVE) drain(WAVE);
+    };
+    const int nw = blockDim.x / WAVE, passes = (end - begin + WAVE - 1) / WAVE;   // none for an empty tile
+    // the row after the current one, loaded ahead (indices clamped to the tile); the
+    // spin sweep has no registers left for it and would wait for the loads to spill them
+    constexpr bool AHEAD = !SPIN;
+    double nx1 = 0.0, nx2 = 0.0, nq1 = 0.0, nq2 = 0.0, nd1 = 0.0, nd2 = 0.0, nA = 0.0, ng = 0.0;
+    auto load_row = [&](int jr) {
+        const int i = min(begin + jr * WAVE + lane, end - 1);
+        nx1 = a.xi1[i];
+        nx2 = a.xi2[i];
+        nq1 = a.p1[i];
+        nq2 = a.p2[i];
+        if constexpr (!FIRST) {
+            nd1 = a.d1[i];
+            nd2 = a.d2[i];
+            nA = a.azn[i];
+            ng = a.gamn[i];
+        }
+    };
+    if (AHEAD && wid < passes) load_row(wid);
+    __syncthreads();
+    for (int jr = wid;; jr += nw) {
+        const bool last = jr >= passes;   // only the waiting particles are left
+        if (!last) {
+            const int i = begin + jr * WAVE + lane;
+            const bool live = i < end;
+            if (!AHEAD) load_row(jr);
+            const double x1 = nx1, x2 = nx2, q1 = nq1, q2 = nq2;
+            double D1 = nd1, D2 = nd2, An = nA, gn = ng;
+            if (AHEAD && jr + nw < passes) load_row(jr + nw);
+            if constexpr (FIRST) {
+                const int c2 = (int)x2;
+                An = start_A<P>(t, x1 - r, x2 - c2, c2);
+                gn = gamma_of(q1, q2, An);
+                const double sc = a.dt * frcp(gn);
+                D1 = q1 * sc;
+                D2 = q2 * sc;
+                if (live) {
+                    a.d1[i] = D1;
+                    a.d2[i] = D2;
+                    a.azn[i] = An;
+                    a.gamn[i] = gn;
+                }
+            }
+            const Step g = make_step(a, x1, x2, q1, q2, D1, D2, r);
+            const bool in = stays(g);
+            const unsigned long long cm = __builtin_amdgcn_ballot_w64(live && !in);
+            if (live && !in) qi[qn + rank_in(cm)] = i;
+            qn += __builtin_popcountll(cm);
+            if (live && in) {
+                const Legs l = legs_of<P, SPIN, false>(g, i, t, a);
+                __builtin_amdgcn_sched_barrier(0);   // each part keeps to its own registers
+                double E1 = 0.0, E2 = 0.0;
+                piece<P>(g, true, 0.0, 1.0, 0, 0, t, a.w, E1, E2);
+                __builtin_amdgcn_sched_barrier(0);
+                push<SPIN>(g, true, i, E1, E2, An, gn, l, a, rmax, flags);
+            }
+        }
+        if (qn >= WAVE || (last && qn > 0)) {
+            // do the first n waiting particles, one per lane, and move the rest up
+            wave_fence();
+            const int n = min(qn, WAVE);
+            const bool valid = lane < n;
+            const int i = qi[valid ? lane : 0];
+            const double x1 = a.xi1[i], x2 = a.xi2[i], q1 = a.p1[i], q2 = a.p2[i];
+            const int c2 = (int)x2;
+            const double An = start_A<P>(t, x1 - r, x2 - c2, c2);
+            double gn = gamma_of(q1, q2, An);
+            asm volatile("" : "+v"(gn));   // formed here, as the legs below
+            double D1, D2;
+            if constexpr (FIRST) {   // as above
+                const double sc = a.dt * frcp(gn);
+                D1 = q1 * sc;
+                D2 = q2 * sc;
+            } else {
+                D1 = a.d1[i];
+                D2 = a.d2[i];
+            }
+            Step g = make_step(a, x1, x2, q1, q2, D1, D2, r);
+            cross_step(g, valid, flags);
+            const Legs l = legs_of<P, SPIN, true>(g, i, t, a);
+            __builtin_amdgcn_sched_barrier(0);
+            double E1 = 0.0, E2 = 0.0;
+            pieces<P>(g, valid, t, a.w, E1, E2);
+            __builtin_amdgcn_sched_barrier(0);
+            push<SPIN>(g, valid, i, E1, E2, An, gn, l, a, rmax, flags);
+            qn -= n;
+            const int mi = qi[WAVE + lane];
+            wave_fence();
+            if (lane < qn) qi[lane] = mi;
+        }
+        if (last) break;
     }
-    if (tail > head) drain(tail - head);
     if (flags) atomicOr(a.flags, flags);
     block_max_to(rmax, a.res);
     __syncthreads();
-    for (int k = threadIdx.x; k < PR * PC; k += blockDim.x) {
+    for (int k = threadIdx.x; k < PS; k += blockDim.x) {
         const int i = k / PC, j = k - i * PC;
+        if (j >= width) continue;
         const int g = wrapi(t.R0 + i, a.M1) * a.M2 + wrapi(t.C0 + j, a.M2);
         if (sJ1[k] != 0.0) atomicAdd(&a.J1[g], sJ1[k]);
         if (sJ2[k] != 0.0) atomicAdd(&a.J2[g], sJ2[k]);
@@ -972,80 +1076,98 @@ __device__ __forceinline__ double new_coord(double u, double d, double inv_dx, i
     return v;
 }
 
-// Subsystem I commit, first half (one block per tile): the new tile Tn and the
-// column c of every particle inside it, packed as Tn 64 + c in word[i]; per
-// tile the particles that stay and (by atomics) those that arrive.  The new
-// positions and momenta are written by the re-sort.
+// A particle's packed place after the commit: the new tile, whether its next step
+// is expected to leave its cell, and its column in the tile.
+__device__ __forceinline__ int pack_place(int Tn, bool leaves, int col) { return (Tn << 7) | (leaves ? 64 : 0) | col; }
+__device__ __forceinline__ int place_tile(int w) { return w >> 7; }
+__device__ __forceinline__ int place_key(int w) { return w & 127; }   // sort key inside the tile
+
+// Subsystem I commit, first half (one block per tile): every particle's place (the
+// next step is expected to move it by the committed increment again, which is off
+// by the step's change of velocity only); per tile the particles that stay and (by
+// atomics) those that arrive, and the tile's leavers listed with the slot each has
+// among its new tile's arrivals.  The new positions and momenta are written by the
+// re-sort.
 __global__ __launch_bounds__(BLOCK) void k2_commit_tiles(const double *__restrict__ xi1,
                                                          const double *__restrict__ xi2,
                                                          const double *__restrict__ d1, const double *__restrict__ d2,
-                                                         int32_t *__restrict__ word,
+                                                         int32_t *__restrict__ word, int2 *__restrict__ leavers,
                                                          const int32_t *__restrict__ tstart, int32_t *__restrict__ tstay,
                                                          int32_t *__restrict__ tarr, int M1, int M2, int TW,
                                                          double inv_dx1, double inv_dx2) {
-    __shared__ int red[BLOCK / WAVE];
+    __shared__ int nleave;
     const int T = blockIdx.x, nseg = M2 / TW;
     const int begin = tstart[T], end = tstart[T + 1];
-    int stay = 0;
-    for (int i = begin + threadIdx.x; i < end; i += blockDim.x) {
-        const double u1 = new_coord(xi1[i], d1[i], inv_dx1, M1), u2 = new_coord(xi2[i], d2[i], inv_dx2, M2);
-        const int c2 = (int)u2, sg = c2 / TW;
-        const int Tn = (int)u1 * nseg + sg;
-        word[i] = (Tn << 6) | (c2 - sg * TW);
-        if (Tn == T) ++stay;
-        wave_claim(tarr, Tn, Tn != T);
-    }
-#pragma unroll
-    for (int o = WAVE / 2; o > 0; o >>= 1) stay += __shfl_xor(stay, o, WAVE);
-    if (lane_id() == 0) red[threadIdx.x / WAVE] = stay;
+    if (threadIdx.x == 0) nleave = 0;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int t = 0;
-        for (int w = 0; w < (int)(blockDim.x / WAVE); ++w) t += red[w];
-        tstay[T] = t;
+    for (int i = begin + threadIdx.x; i < end; i += blockDim.x) {
+        const double e1 = d1[i], e2 = d2[i];
+        const double u1 = new_coord(xi1[i], e1, inv_dx1, M1), u2 = new_coord(xi2[i], e2, inv_dx2, M2);
+        const int c1 = (int)u1, c2 = (int)u2, sg = c2 / TW;
+        const int Tn = c1 * nseg + sg;
+        const double v1 = fma(e1, inv_dx1, u1) - c1, v2 = fma(e2, inv_dx2, u2) - c2;
+        word[i] = pack_place(Tn, !(v1 >= 0.0 && v1 < 1.0 && v2 >= 0.0 && v2 < 1.0), c2 - sg * TW);
+        const bool go = Tn != T;
+        const int slot = wave_claim(tarr, Tn, go);
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(go);
+        if (m) {   // one counter update per wave
+            const int leader = __builtin_ctzll(m);
+            int at = 0;
+            if (lane_id() == leader) at = atomicAdd(&nleave, __builtin_popcountll(m));
+            at = __shfl(at, leader, WAVE);
+            if (go) leavers[begin + at + rank_in(m)] = make_int2(i, slot);
+        }
     }
+    __syncthreads();
+    if (threadIdx.x == 0) tstay[T] = end - begin - nleave;
 }
 
-// count[T] = stay[T] + arrivals[T]; the arrival counts and cursors start at zero again.
+// count[T] = stay[T] + arrivals[T]; the arrival counts start at zero again.
 __global__ void k2_tile_counts(const int32_t *__restrict__ tstay, int32_t *__restrict__ tarr,
-                               int32_t *__restrict__ tcnt, int32_t *__restrict__ tcur, int ntiles) {
+                               int32_t *__restrict__ tcnt, int ntiles) {
     for (int T = blockIdx.x * blockDim.x + threadIdx.x; T < ntiles; T += gridDim.x * blockDim.x) {
         tcnt[T] = tstay[T] + tarr[T];
         tarr[T] = 0;
-        tcur[T] = 0;
     }
 }
 
-// Arrivals listed per new tile: a particle of old tile T whose new tile Tn
-// differs puts its index at mig[tnew[Tn] + tstay[Tn] + k], k from Tn's cursor
-// (the slots after Tn's stayers in the new order).
-__global__ __launch_bounds__(BLOCK) void k2_list_arrivals(const int32_t *__restrict__ word,
-                                                          const int32_t *__restrict__ told,
-                                                          const int32_t *__restrict__ tnew,
-                                                          const int32_t *__restrict__ tstay, int32_t *__restrict__ tcur,
-                                                          int32_t *__restrict__ mig) {
-    const int T = blockIdx.x;
-    for (int i = told[T] + threadIdx.x; i < told[T + 1]; i += blockDim.x) {
-        const int Tn = word[i] >> 6;
-        const int k = wave_claim(tcur, Tn, Tn != T);
-        if (Tn != T) mig[tnew[Tn] + tstay[Tn] + k] = i;
+// Arrivals listed per new tile: a leaver of old tile T puts its index at
+// mig[tnew[Tn] + tstay[Tn] + slot] (the places after Tn's stayers in the new order).
+__global__ __launch_bounds__(WAVE) void k2_list_arrivals(const int32_t *__restrict__ word,
+                                                         const int2 *__restrict__ leavers,
+                                                         const int32_t *__restrict__ told,
+                                                         const int32_t *__restrict__ tnew,
+                                                         const int32_t *__restrict__ tstay, int32_t *__restrict__ mig) {
+    const int T = blockIdx.x, begin = told[T], n = told[T + 1] - begin - tstay[T];
+    for (int k = threadIdx.x; k < n; k += blockDim.x) {
+        const int2 l = leavers[begin + k];
+        const int Tn = place_tile(word[l.x]);
+        mig[tnew[Tn] + tstay[Tn] + l.y] = l.x;
     }
 }
 
 // Subsystem I commit, second half, and the re-sort in one pass (one block per
 // new tile): the tile's particles are the stayers of its old range and its
-// listed arrivals; an LDS histogram of their new columns and its prefix give
-// each its rank in the cell-sorted order, and the tile is written in the
-// transposed layout (tile_pos), so that a coalesced read hands the lanes of a
-// wave particles of different cells.  Each particle is written with its new
-// position (formed again from x^n and the increment), its momentum p^(k+1)
-// and its id.  When the tile's sources and particles fit INVCAP, every output
-// array passes through LDS (sources read in order, values placed at their new
-// positions, the tile written in order); a fuller tile writes each particle to
-// its position directly.
-constexpr int INVCAP = 6144;
-
-constexpr int SORT_THREADS = 512;
+// listed arrivals.  They are ordered by the sort key: those expected to stay in
+// their cell by column, then those expected to leave it by column, each of the two
+// parts in the transposed layout (tile_pos), so that a coalesced read hands the
+// lanes of a wave particles of different cells and (for the sweep) of one kind.
+// An LDS counter per key gives each particle its rank (in any order), the prefix
+// over the keys its place.  Each particle is written with its new position
+// (formed again from x^n and the increment), its momentum p^(k+1) and its id.
+// When the tile's sources and particles fit INVCAP, every output array passes
+// through LDS (sources read in order, values placed at their new positions, the
+// tile written in order), the next array's values being loaded into registers
+// while one is written; a fuller tile writes each particle to its position
+// directly.  Latency-bound on its barriers: with the scans and the arrival lists
+// 366 us at 2^24 particles for 1024 threads of 6 sources (106 registers, one
+// block per CU), 570 us for 512 of 12 (spilling at two blocks per CU); stable
+// ranks by wave ballots in the old order, with the values loaded between the
+// barriers, took 700 us.
+constexpr int SORT_THREADS = 1024;
+constexpr int SORT_PER = 6;   // sources per thread
+constexpr int INVCAP = SORT_THREADS * SORT_PER;
+constexpr int NKEY = 128;
 
 struct Resort {
     const double *xi1, *xi2, *d1, *d2, *pk1, *pk2;
@@ -1056,6 +1178,33 @@ struct Resort {
     double inv_dx1, inv_dx2;
     const double *ss[3];   // spins (null without spin)
     double *os[3];
+    // output array f of the sources i[k] >= 0, all loads issued before any is used
+    template <int N>
+    __device__ __forceinline__ void values(int f, const int (&i)[N], double (&v)[N]) const {
+        auto from = [&](const double *x) {
+#pragma unroll
+            for (int k = 0; k < N; ++k) v[k] = i[k] >= 0 ? x[i[k]] : 0.0;
+        };
+        auto coord = [&](const double *x, const double *d, double inv_dx, int M) {
+            double e[N];
+            from(x);
+#pragma unroll
+            for (int k = 0; k < N; ++k) e[k] = i[k] >= 0 ? d[i[k]] : 0.0;
+#pragma unroll
+            for (int k = 0; k < N; ++k) v[k] = new_coord(v[k], e[k], inv_dx, M);
+        };
+        switch (f) {
+            case 0: coord(xi1, d1, inv_dx1, M1); break;
+            case 1: coord(xi2, d2, inv_dx2, M2); break;
+            case 2: from(pk1); break;
+            case 3: from(pk2); break;
+            case 4:
+#pragma unroll
+                for (int k = 0; k < N; ++k) v[k] = i[k] >= 0 ? (double)sid[i[k]] : 0.0;
+                break;
+            default: from(ss[f - 5]); break;
+        }
+    }
     __device__ __forceinline__ void put(int j, int i) const {
         o1[j] = new_coord(xi1[i], d1[i], inv_dx1, M1);
         o2[j] = new_coord(xi2[i], d2[i], inv_dx2, M2);
@@ -1067,126 +1216,91 @@ struct Resort {
     }
 };
 
-// Particles per thread whose loads the re-sort issues together.
-constexpr int RB = 4;
-
-__global__ __launch_bounds__(SORT_THREADS) void k2_tile_resort(Resort a) {
-    constexpr int NW = SORT_THREADS / WAVE;
-    __shared__ int hist[WAVE], cur[WAVE];
-    __shared__ int wcnt[NW][WAVE], woff[NW][WAVE];
-    __shared__ int pos[INVCAP];      // new position in the tile of source q (-1: it left)
-    __shared__ double val[INVCAP];   // one output array of the tile, by new position
+__global__ __launch_bounds__(SORT_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k2_tile_resort(Resort a) {
+    __shared__ int hist[NKEY], first[NKEY];   // particles of a key; their first rank
+    __shared__ double val[INVCAP];            // one output array of the tile, by new position
     const int T = tile_of_block();
     const int ob = a.told[T], nold = a.told[T + 1] - ob;
     const int base = a.tnew[T], cnt = a.tnew[T + 1] - base, arr0 = base + a.tstay[T];
     const int nsrc = nold + cnt - a.tstay[T];
-    const int nt = blockDim.x, wv = threadIdx.x / WAVE;
+    const int nt = SORT_THREADS, t0 = threadIdx.x;
     // source q < nold: old position q of the tile; q >= nold: listed arrival
     auto source = [&](int q) { return q < nold ? ob + q : a.mig[arr0 + q - nold]; };
-    if (threadIdx.x < WAVE) hist[threadIdx.x] = 0;
-    for (int k = threadIdx.x; k < NW * WAVE; k += nt) wcnt[k / WAVE][k % WAVE] = 0;
+    for (int k = t0; k < NKEY; k += nt) hist[k] = 0;
     __syncthreads();
-    // column counts (any order)
-    for (int q0 = threadIdx.x; q0 < nsrc; q0 += RB * nt) {
-        int w[RB];
+    const bool direct = cnt > INVCAP || nsrc > INVCAP;   // uniform over the block
+    int src[SORT_PER], pos[SORT_PER];   // source index (-1: none, or it left) and rank, later position
+    if (!direct) {
 #pragma unroll
-        for (int k = 0; k < RB; ++k) w[k] = q0 + k * nt < nsrc ? a.word[source(q0 + k * nt)] : -1;
+        for (int k = 0; k < SORT_PER; ++k) {
+            const int q = t0 + k * nt;
+            src[k] = q < nsrc ? source(q) : -1;
+        }
+        int w[SORT_PER];
 #pragma unroll
-        for (int k = 0; k < RB; ++k)
-            if (w[k] >= 0 && (w[k] >> 6) == T) atomicAdd(&hist[w[k] & 63], 1);
+        for (int k = 0; k < SORT_PER; ++k) w[k] = src[k] >= 0 ? a.word[src[k]] : -1;
+#pragma unroll
+        for (int k = 0; k < SORT_PER; ++k) {
+            pos[k] = 0;
+            if (w[k] >= 0 && place_tile(w[k]) == T)
+                pos[k] = (place_key(w[k]) << 16) | atomicAdd(&hist[place_key(w[k])], 1);
+            else
+                src[k] = -1;
+        }
+    } else {
+        for (int q = t0; q < nsrc; q += nt) {
+            const int w = a.word[source(q)];
+            if (place_tile(w) == T) atomicAdd(&hist[place_key(w)], 1);
+        }
     }
     __syncthreads();
-    if (threadIdx.x < WAVE) {   // exclusive prefix over the 64 columns
-        const int v = hist[threadIdx.x];
-        int inc = v;
+    if (t0 < WAVE) {   // exclusive prefix over the keys, two per lane
+        const int v0 = hist[2 * t0], v1 = hist[2 * t0 + 1];
+        int inc = v0 + v1;
 #pragma unroll
         for (int o = 1; o < WAVE; o <<= 1) {
             const int u = __shfl_up(inc, o, WAVE);
-            if ((int)threadIdx.x >= o) inc += u;
+            if (t0 >= o) inc += u;
         }
-        cur[threadIdx.x] = inc - v;
+        first[2 * t0] = inc - v0 - v1;
+        first[2 * t0 + 1] = inc - v1;
     }
     __syncthreads();
-    // Stable ranks: the sources in the old cell-sorted order (old rank t at
-    // position tile_pos(t)), then the arrivals, a block of them at a time;
-    // inside a wave the lanes of one column count the lower lanes of that
-    // column, across waves a per-column prefix.  Rank r goes to position
-    // tile_pos(r) of the new tile.
-    const bool direct = cnt > INVCAP || nsrc > INVCAP;
-    for (int t0 = 0; t0 < nsrc; t0 += nt) {   // uniform over the block
-        const int t = t0 + threadIdx.x;
-        int q = -1, key = -1;
-        if (t < nsrc) {
-            q = t < nold ? tile_pos(t, nold) : t;
-            const int w = a.word[source(q)];
-            if ((w >> 6) == T) key = w & 63;
+    const int nin = first[NKEY / 2];   // particles expected to stay in their cell
+    auto place = [&](int rank) { return rank < nin ? tile_pos(rank, nin) : nin + tile_pos(rank - nin, cnt - nin); };
+    if (direct) {
+        for (int q = t0; q < nsrc; q += nt) {
+            const int i = source(q), w = a.word[i];
+            if (place_tile(w) == T) a.put(base + place(atomicAdd(&first[place_key(w)], 1)), i);
         }
-        unsigned long long rem = __builtin_amdgcn_ballot_w64(key >= 0);
-        int wr = 0;
-        while (rem) {
-            const int leader = __builtin_ctzll(rem);
-            const int lk = __shfl(key, leader, WAVE);
-            const unsigned long long m = __builtin_amdgcn_ballot_w64(key == lk);
-            if (key == lk) wr = rank_in(m);
-            if (lane_id() == leader) wcnt[wv][lk] = __builtin_popcountll(m);
-            rem &= ~m;
-        }
-        __syncthreads();
-        if (threadIdx.x < WAVE) {
-            int run = cur[threadIdx.x];
-            for (int v = 0; v < NW; ++v) {
-                const int c = wcnt[v][threadIdx.x];
-                wcnt[v][threadIdx.x] = 0;
-                woff[v][threadIdx.x] = run;
-                run += c;
-            }
-            cur[threadIdx.x] = run;
-        }
-        __syncthreads();
-        if (q >= 0) {
-            const int p = key >= 0 ? tile_pos(woff[wv][key] + wr, cnt) : -1;
-            if (direct) {
-                if (p >= 0) a.put(base + p, source(q));
-            } else {
-                pos[q] = p;
-            }
+        return;
+    }
+    {
+        // place() without its integer divisions: t / Q as (t + 1/2) times the float
+        // 1 / Q, exact for t < INVCAP (the error stays below half of 1 / Q)
+        const int Qi = nin / WAVE, Qo = (cnt - nin) / WAVE;
+        const float ri = Qi ? 1.0f / (float)Qi : 0.0f, ro = Qo ? 1.0f / (float)Qo : 0.0f;
+#pragma unroll
+        for (int k = 0; k < SORT_PER; ++k) {
+            const int rank = first[pos[k] >> 16] + (pos[k] & 0xffff);
+            const bool in = rank < nin;
+            const int t = in ? rank : rank - nin, Q = in ? Qi : Qo;
+            const int l = (int)(((float)t + 0.5f) * (in ? ri : ro));
+            pos[k] = (in ? 0 : nin) + (t < WAVE * Q ? (t - l * Q) * WAVE + l : t);
         }
     }
-    if (direct) return;   // uniform over the block
-    // One output array at a time: the old tile read in order (and the
-    // arrivals), each value placed in LDS at its new position, the tile written
-    // in order.
     const int nf = a.ss[0] ? 8 : 5;   // with spin: s_x, s_y, s_z as well
+    double v[SORT_PER];
+    a.values(0, src, v);
     for (int f = 0; f < nf; ++f) {
-        __syncthreads();
-        for (int q0 = threadIdx.x; q0 < nsrc; q0 += RB * nt) {
-            int i[RB], p[RB];
-            double v[RB];
+        if (f > 0) __syncthreads();   // the previous array is written
 #pragma unroll
-            for (int k = 0; k < RB; ++k) {
-                const int q = q0 + k * nt;
-                p[k] = q < nsrc ? pos[q] : -1;
-                i[k] = p[k] >= 0 ? source(q) : -1;
-            }
-#pragma unroll
-            for (int k = 0; k < RB; ++k) {
-                if (i[k] < 0) continue;
-                switch (f) {
-                    case 0: v[k] = new_coord(a.xi1[i[k]], a.d1[i[k]], a.inv_dx1, a.M1); break;
-                    case 1: v[k] = new_coord(a.xi2[i[k]], a.d2[i[k]], a.inv_dx2, a.M2); break;
-                    case 2: v[k] = a.pk1[i[k]]; break;
-                    case 3: v[k] = a.pk2[i[k]]; break;
-                    case 4: v[k] = (double)a.sid[i[k]]; break;
-                    default: v[k] = a.ss[f - 5][i[k]]; break;
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < RB; ++k)
-                if (i[k] >= 0) val[p[k]] = v[k];
-        }
+        for (int k = 0; k < SORT_PER; ++k)
+            if (src[k] >= 0) val[pos[k]] = v[k];
+        if (f + 1 < nf) a.values(f + 1, src, v);
         __syncthreads();
         double *out = f == 0 ? a.o1 : f == 1 ? a.o2 : f == 2 ? a.r1 : f == 3 ? a.r2 : f == 4 ? nullptr : a.os[f - 5];
-        for (int p = threadIdx.x; p < cnt; p += nt) {
+        for (int p = t0; p < cnt; p += nt) {
             if (f != 4) out[base + p] = val[p];
             else a.did[base + p] = (int32_t)val[p];
         }
@@ -1925,7 +2039,7 @@ struct ecpic2d_ctx {
     int32_t *cell = nullptr /* new cell (set_particles) or packed new tile and column (commit) */, *count = nullptr,
             *start = nullptr, *bsum = nullptr;
     int32_t *mig = nullptr;   // arrivals per new tile, after the stayers' slots
-    int32_t *tstart[2] = {}, *tstay = nullptr, *tarr = nullptr, *tcnt = nullptr, *tcur = nullptr;
+    int32_t *tstart[2] = {}, *tstay = nullptr, *tarr = nullptr, *tcnt = nullptr;
     int ts = 0, ntiles = 0;   // tstart[ts]: first particle of each tile
     double *e1 = nullptr, *e2 = nullptr, *bz = nullptr, *ez = nullptr, *az = nullptr;
     double *en1 = nullptr, *en2 = nullptr, *ek1 = nullptr, *ek2 = nullptr, *eb1 = nullptr, *eb2 = nullptr;
@@ -2023,20 +2137,22 @@ void sort_particles(ecpic2d_ctx *c) {
     c->cur = B;
 }
 
-// Re-sort after the first half of a Subsystem I commit (packed new tile and
-// column in c->cell, stay and arrival counts per tile; increment in buffer di):
+// The commit's list of leavers takes the increment buffer that is not committed.
+int2 *leavers_of(ecpic2d_ctx *c, int di) { return reinterpret_cast<int2 *>(c->d1[1 - di]); }
+
+// Re-sort after the first half of a Subsystem I commit (places in c->cell, stay and arrival counts per tile; increment in buffer di):
 // new tile starts, the arrival lists, then each new tile formed and sorted by
 // cell into the transposed layout in the other particle buffer.
 void sort_tiles(ecpic2d_ctx *c, int di) {
     const int A = c->cur, B = 1 - c->cur, T0 = c->ts, T1 = 1 - c->ts;
     timed(c, "sort", [&] {
         const int nt = c->ntiles, nb = (nt + SCAN_TILE - 1) / SCAN_TILE;
-        k2_tile_counts<<<grid_for(nt), BLOCK, 0, c->stream>>>(c->tstay, c->tarr, c->tcnt, c->tcur, nt);
+        k2_tile_counts<<<grid_for(nt), BLOCK, 0, c->stream>>>(c->tstay, c->tarr, c->tcnt, nt);
         k2_scan_sums<<<nb, SCAN_THREADS, 0, c->stream>>>(c->tcnt, c->bsum, nt);
         k2_scan_top<<<1, SCAN_THREADS, 0, c->stream>>>(c->bsum, nb, c->tstart[T1] + nt);
         k2_scan_apply<<<nb, SCAN_THREADS, 0, c->stream>>>(c->tcnt, c->tstart[T1], c->bsum, nt);
-        k2_list_arrivals<<<nt, BLOCK, 0, c->stream>>>(c->cell, c->tstart[T0], c->tstart[T1], c->tstay, c->tcur,
-                                                     c->mig);
+        k2_list_arrivals<<<nt, WAVE, 0, c->stream>>>(c->cell, leavers_of(c, di), c->tstart[T0], c->tstart[T1],
+                                                    c->tstay, c->mig);
         const Resort r{c->xi1[A], c->xi2[A], c->d1[di], c->d2[di], c->pk1, c->pk2, c->id[A], c->cell, c->mig,
                        c->tstart[T0], c->tstart[T1], c->tstay, c->xi1[B], c->xi2[B], c->p1[B], c->p2[B], c->id[B],
                        c->M1, c->M2, 1.0 / c->dx1, 1.0 / c->dx2, {c->sx[A], c->sy[A], c->sz[A]},
@@ -2173,7 +2289,7 @@ int substep_I(ecpic2d_ctx *c, double dt, ecpic2d_iter_stats *st) {
     // fields, then the re-sort writes the particles in their new order
     timed(c, "commit_I", [&] {
         k2_commit_tiles<<<c->ntiles, BLOCK, 0, s>>>(c->xi1[A], c->xi2[A], c->d1[di], c->d2[di], c->cell,
-                                                    c->tstart[c->ts], c->tstay, c->tarr, c->M1, c->M2, c->TW,
+                                                    leavers_of(c, di), c->tstart[c->ts], c->tstay, c->tarr, c->M1, c->M2, c->TW,
                                                     1.0 / c->dx1, 1.0 / c->dx2);
     });
     k2_copy<<<gC, BLOCK, 0, s>>>(c->e1, c->ek1, Nc);
@@ -2353,7 +2469,7 @@ int ecpic2d_create(const ecpic2d_config *cfg, ecpic2d_ctx **out) {
     c->ntiles = c->M1 * (c->M2 / c->TW);
     rc |= dalloc(c, &c->tstart[0], (size_t)c->ntiles + 1) | dalloc(c, &c->tstart[1], (size_t)c->ntiles + 1) |
           dalloc(c, &c->tstay, (size_t)c->ntiles) | dalloc(c, &c->tarr, (size_t)c->ntiles) |
-          dalloc(c, &c->tcnt, (size_t)c->ntiles) | dalloc(c, &c->tcur, (size_t)c->ntiles);
+          dalloc(c, &c->tcnt, (size_t)c->ntiles);
     double **grids[] = {&c->e1, &c->e2, &c->bz, &c->ez, &c->az, &c->en1, &c->en2, &c->ek1, &c->ek2, &c->eb1,
                         &c->eb2, &c->J1, &c->J2, &c->g1a, &c->g2a, &c->ezn, &c->ezk, &c->S, &c->tmp};
     for (double **gp : grids) rc |= dalloc(c, gp, Nc);
@@ -2406,7 +2522,7 @@ int ecpic2d_create(const ecpic2d_config *cfg, ecpic2d_ctx **out) {
     for (double **gp : grids) k2_fill<<<grid_for(c->Nc), BLOCK, 0, c->stream>>>(*gp, c->Nc, 0.0);
     k2_fill_i32<<<grid_for(c->Nc), BLOCK, 0, c->stream>>>(c->count, c->Nc);
     // the commit accumulates arrivals per tile: every tile counter starts at zero
-    for (int32_t *tp : {c->tstay, c->tarr, c->tcnt, c->tcur})
+    for (int32_t *tp : {c->tstay, c->tarr, c->tcnt})
         k2_fill_i32<<<grid_for(c->ntiles), BLOCK, 0, c->stream>>>(tp, c->ntiles);
     k2_fill_i32<<<1, 1, 0, c->stream>>>(c->flags, 1);
     if (sync2(c)) { ecpic2d_destroy(c); return ECPIC_EDEVICE; }
@@ -2449,7 +2565,7 @@ int ecpic2d_set_particles(ecpic2d_ctx *c, const double *x1, const double *x2, co
     (void)B;
     k2_fill_i32<<<1, 1, 0, s>>>(c->flags, 1);
     k2_fill_i32<<<grid_for(c->Nc), BLOCK, 0, s>>>(c->count, c->Nc);
-    for (int32_t *tp : {c->tstay, c->tarr, c->tcnt, c->tcur})
+    for (int32_t *tp : {c->tstay, c->tarr, c->tcnt})
         k2_fill_i32<<<grid_for(c->ntiles), BLOCK, 0, s>>>(tp, c->ntiles);
     k2_iota<<<grid_for(n), BLOCK, 0, s>>>(c->id[A], n);
     k2_bin_new<<<grid_for(n), BLOCK, 0, s>>>(c->d1[0], c->d2[0], c->xi1[A], c->xi2[A], c->cell, c->count, n,
