@@ -72,7 +72,7 @@ __device__ __forceinline__ unsigned long long bitsd(double v) { return (unsigned
 
 // Max of v >= 0 over the block, then one atomic max (as bits) into *slot.
 __device__ __forceinline__ void block_max_to(double v, unsigned long long *slot) {
-    __shared__ double red[BLOCK / WAVE];
+    __shared__ double red[1024 / WAVE];
 #pragma unroll
     for (int o = WAVE / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, WAVE));
     const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;
@@ -83,6 +83,14 @@ __device__ __forceinline__ void block_max_to(double v, unsigned long long *slot)
         for (int w = 1; w < (int)(blockDim.x / WAVE); ++w) m = fmax(m, red[w]);
         if (m > 0.0) atomicMax(slot, bitsd(m));
     }
+}
+
+// The vector memory operations this thread has issued are complete (device-scope
+// atomics then have been performed where every block sees them).
+__device__ __forceinline__ void wait_memory() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
 }
 
 // Sum over the block in a fixed order; thread 0 writes it to *out.
@@ -106,6 +114,15 @@ __device__ __forceinline__ int tile_of_block() {
     const int b = blockIdx.x, n = gridDim.x;
     if (n % 8 != 0) return b;
     return (b % 8) * (n / 8) + b / 8;
+}
+
+// The same with `split` blocks per tile (all on one XCD): the tile, and which share of
+// its rows of 64 particles the block takes (wave w of part q takes every
+// split * waves-th row from row q * waves + w on).
+__device__ __forceinline__ int tile_of_block(int split, int &part) {
+    const int b = tile_of_block(), t = b / split;
+    part = b - t * split;
+    return t;
 }
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (WAVE - 1)); }
@@ -212,11 +229,6 @@ __global__ void k2_fill_i32(int32_t *a, int64_t n) {
         a[i] = 0;
 }
 
-__global__ void k2_copy(double *__restrict__ dst, const double *__restrict__ src, int64_t n) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        dst[i] = src[i];
-}
-
 // (G a)_1 = (a_{i1,i2} - a_{i1-1,i2}) / dx1, (G a)_2 = (a_{i1,i2} - a_{i1,i2-1}) / dx2.
 __global__ void k2_grad(const double *__restrict__ a, double *__restrict__ g1, double *__restrict__ g2, int M1,
                         int M2, double inv_dx1, double inv_dx2) {
@@ -226,6 +238,51 @@ __global__ void k2_grad(const double *__restrict__ a, double *__restrict__ g1, d
         const double v = a[i];
         g1[i] = (v - a[wrapi(i1 - 1, M1) * M2 + i2]) * inv_dx1;
         g2[i] = (v - a[i1 * M2 + wrapi(i2 - 1, M2)]) * inv_dx2;
+    }
+}
+
+// Start of Subsystem I: G a_z, the field iterates e^(0) = e^n and their mean with e^n,
+// the current accumulators, residual slots, flags and gate, in one pass.
+struct BeginI {
+    const double *az, *e1, *e2;
+    double *g1, *g2, *ek1, *ek2, *eb1, *eb2, *J1, *J2;
+    unsigned long long *res;
+    int nres, *flags, *gate;
+    int M1, M2;
+    double inv_dx1, inv_dx2;
+};
+
+__global__ void k2_begin_I(BeginI a) {
+    const int N = a.M1 * a.M2, t0 = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+    for (int i = t0; i < a.nres; i += nt) a.res[i] = 0ull;
+    if (t0 == 0) *a.flags = *a.gate = 0;
+    for (int i = t0; i < N; i += nt) {
+        const int i1 = i / a.M2, i2 = i - i1 * a.M2;
+        const double v = a.az[i];
+        a.g1[i] = (v - a.az[wrapi(i1 - 1, a.M1) * a.M2 + i2]) * a.inv_dx1;
+        a.g2[i] = (v - a.az[i1 * a.M2 + wrapi(i2 - 1, a.M2)]) * a.inv_dx2;
+        const double e1 = a.e1[i], e2 = a.e2[i];
+        a.ek1[i] = e1;
+        a.ek2[i] = e2;
+        a.eb1[i] = e1;
+        a.eb2[i] = e2;
+        a.J1[i] = 0.0;
+        a.J2[i] = 0.0;
+    }
+}
+
+// Start of Subsystem III: e^n and the iterate e^(0) = e^n, the accumulator, residual
+// slots and gate.
+__global__ void k2_begin_III(const double *__restrict__ ez, double *__restrict__ ezn, double *__restrict__ ezk,
+                             double *__restrict__ S, int N, unsigned long long *res, int nres, int *gate) {
+    const int t0 = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+    for (int i = t0; i < nres; i += nt) res[i] = 0ull;
+    if (t0 == 0) *gate = 0;
+    for (int i = t0; i < N; i += nt) {
+        const double e = ez[i];
+        ezn[i] = e;
+        ezk[i] = e;
+        S[i] = 0.0;
     }
 }
 
@@ -440,11 +497,12 @@ __global__ __launch_bounds__(BLOCK) void k2_deposit_spin(const double *__restric
                                                          const double *__restrict__ sz,
                                                          const int32_t *__restrict__ start, double *__restrict__ Dx,
                                                          double *__restrict__ Dy, double *__restrict__ Dz, int M1,
-                                                         int M2, int TW, double w, int mode) {
+                                                         int M2, int TW, double w, int mode, int split) {
     constexpr int PR = P + 1, PCM = TWMAX + P, PS = PR * PCM;
     __shared__ double sX[PS], sY[PS];
     const int nseg = M2 / TW;
-    const int tile = tile_of_block();
+    int part;
+    const int tile = tile_of_block(split, part);
     const int r = tile / nseg, c0 = (tile - r * nseg) * TW;
     const int PC = TW + P;
     const int R0 = r - P, C0 = c0 - P;
@@ -454,7 +512,7 @@ __global__ __launch_bounds__(BLOCK) void k2_deposit_spin(const double *__restric
     }
     __syncthreads();
     const int begin = start[tile], end = start[tile + 1];
-    for (int i = begin + threadIdx.x; i < end; i += blockDim.x) {
+    for (int i = begin + part * BLOCK + threadIdx.x; i < end; i += split * BLOCK) {
         const double u1 = xi1[i], u2 = xi2[i];
         const int c2 = (int)u2;
         double a1[P + 1], a2[P + 1], b1[P], b2[P];
@@ -526,6 +584,8 @@ struct SweepArgs {
     const double *sx, *sy, *sz, *bz;     // spins and b_z (the sweep with spin)
     double hbar;
     double *azn, *gamn;                  // A_z(x^n) and gamma(x^n, p^n): formed by sweep 0, read by the rest
+    int keep_p;                          // store p^(k+1)
+    int split;                           // blocks per tile
 };
 
 // Line mean of the V1 basis (degree P-1) along one leg of the step, from t0 in
@@ -886,8 +946,10 @@ __device__ __forceinline__ void push(const Step &g, bool live, int i, double E1,
         if (!isfinite(e1 + e2 + n1 + n2)) flags |= FLAG_NONFINITE;
         a.dn1[i] = e1;
         a.dn2[i] = e2;
-        a.pk1[i] = n1;
-        a.pk2[i] = n2;
+        if (a.keep_p) {
+            a.pk1[i] = n1;
+            a.pk2[i] = n2;
+        }
         rmax = fmax(rmax, fmax(fabs(e1 - g.D1), fabs(e2 - g.D2)));
     }
 }
@@ -903,10 +965,12 @@ __device__ __forceinline__ void push(const Step &g, bool live, int i, double E1,
 // still in cache when it is read again, and stores cover whole lines.
 //
 // Bound by HBM and by the latency of its dependent chains at two or three waves
-// per SIMD (registers); at 512 x 512 cells, 2^24 particles, degree 3: 96 B per
-// particle, about 560 vector and 72 LDS instructions per row of 64 (917 and 87
-// with the general terms run for every lane), 478 us per launch against 660 us
-// with crossing particles inline in any order and the general terms (events).
+// per SIMD (registers); at 512 x 512 cells, 2^24 particles, degree 3: 80 B per
+// particle (96 when it stores its momentum), about 590 vector and 61 LDS
+// instructions per row of 64 (917 and 87 with the general terms run for every
+// lane), 460 us per launch against 660 us with crossing particles inline in any
+// order, the general terms and every momentum stored (events).  Counters: vector
+// units 62 %, LDS 73 % busy, 1.43 GB moved.
 // Taking the 24 LDS atomics out would give 50 us.  More waves do not help when
 // their registers spill: 629 us at four waves per SIMD (degree 3).
 constexpr int QCAP = 2 * WAVE;   // fewer than 64 wait when a row starts
@@ -926,7 +990,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(P <= 3 ? 
     __shared__ double sE1[PS], sE2[PS], sA[PS], sG1[PS], sG2[PS], sJ1[PS], sJ2[PS], sBz[SPIN ? PS : 1];
     __shared__ int qI[BLOCK / WAVE][QCAP];
     const int nseg = a.M2 / a.TW;
-    const int tile = tile_of_block();
+    int part;
+    const int tile = tile_of_block(a.split, part);
     const int r = tile / nseg, c0 = (tile - r * nseg) * a.TW;
     const int width = a.TW + P + 2;   // columns of the patch in use
     const PT t{sE1, sE2, sA, sG1, sG2, sJ1, sJ2, sBz, r - P - 1, c0 - P - 1, r};
@@ -954,7 +1019,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(P <= 3 ? 
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
-    const int nw = blockDim.x / WAVE, passes = (end - begin + WAVE - 1) / WAVE;   // none for an empty tile
+    const int passes = (end - begin + WAVE - 1) / WAVE;   // none for an empty tile
+    const int w0 = part * (BLOCK / WAVE) + wid, nw = a.split * (BLOCK / WAVE);
     // the row after the current one, loaded ahead (indices clamped to the tile); the
     // spin sweep has no registers left for it and would wait for the loads to spill them
     constexpr bool AHEAD = !SPIN;
@@ -972,9 +1038,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(P <= 3 ? 
             ng = a.gamn[i];
         }
     };
-    if (AHEAD && wid < passes) load_row(wid);
+    if (AHEAD && w0 < passes) load_row(w0);
     __syncthreads();
-    for (int jr = wid;; jr += nw) {
+    for (int jr = w0;; jr += nw) {
         const bool last = jr >= passes;   // only the waiting particles are left
         if (!last) {
             const int i = begin + jr * WAVE + lane;
@@ -1122,14 +1188,30 @@ __global__ __launch_bounds__(BLOCK) void k2_commit_tiles(const double *__restric
     if (threadIdx.x == 0) tstay[T] = end - begin - nleave;
 }
 
-// count[T] = stay[T] + arrivals[T]; the arrival counts start at zero again.
-__global__ void k2_tile_counts(const int32_t *__restrict__ tstay, int32_t *__restrict__ tarr,
-                               int32_t *__restrict__ tcnt, int ntiles) {
-    for (int T = blockIdx.x * blockDim.x + threadIdx.x; T < ntiles; T += gridDim.x * blockDim.x) {
-        tcnt[T] = tstay[T] + tarr[T];
-        tarr[T] = 0;
+// Tile starts of the new order: the exclusive scan of stay + arrivals over the
+// tiles (at most SCAN_TILE: one block); the arrival counts start at zero again.
+__global__ __launch_bounds__(SCAN_THREADS) void k2_scan_tiles(const int32_t *__restrict__ tstay,
+                                                              int32_t *__restrict__ tarr,
+                                                              int32_t *__restrict__ tstart, int ntiles) {
+    const int T0 = threadIdx.x * SCAN_PER;
+    int k[SCAN_PER], v = 0;
+#pragma unroll
+    for (int q = 0; q < SCAN_PER; ++q) {
+        k[q] = T0 + q < ntiles ? tstay[T0 + q] + tarr[T0 + q] : 0;
+        v += k[q];
     }
+    int tot;
+    int off = block_exscan1024(v, &tot);
+#pragma unroll
+    for (int q = 0; q < SCAN_PER; ++q)
+        if (T0 + q < ntiles) {
+            tstart[T0 + q] = off;
+            off += k[q];
+            tarr[T0 + q] = 0;
+        }
+    if (threadIdx.x == 0) tstart[ntiles] = tot;
 }
+static_assert((MAXM / TWMAX) * MAXM <= SCAN_TILE && MAXM <= SCAN_TILE, "one block scans the tiles of any grid");
 
 // Arrivals listed per new tile: a leaver of old tile T puts its index at
 // mig[tnew[Tn] + tstay[Tn] + slot] (the places after Tn's stayers in the new order).
@@ -1323,6 +1405,7 @@ struct DepArgs {
     int mode;            // 0: charge w Lambda0; 1: Subsystem III source
     int first;           // III: first iteration of the substep
     const int *gate;     // III: nonzero once an earlier iteration converged (nothing to do)
+    int split;           // blocks per tile
 };
 
 // mode 1: S += w (A^n + A^(k)) / (gamma(p, A^n) + gamma(p, A^(k))) Lambda0(x_a),
@@ -1333,7 +1416,8 @@ __global__ __launch_bounds__(BLOCK) void k2_deposit0(DepArgs a) {
     constexpr int PR = P + 1, PCM = TWMAX + P, PS = PR * PCM;
     __shared__ double sAn[PS], sAk[PS], sS[PS];
     const int nseg = a.M2 / a.TW;
-    const int tile = tile_of_block();
+    int part;
+    const int tile = tile_of_block(a.split, part);
     const int r = tile / nseg, c0 = (tile - r * nseg) * a.TW;
     const int PC = a.TW + P;
     const int R0 = r - P, C0 = c0 - P;
@@ -1349,8 +1433,9 @@ __global__ __launch_bounds__(BLOCK) void k2_deposit0(DepArgs a) {
     }
     __syncthreads();
     const int begin = a.start[tile], end = a.start[tile + 1];
-    const int nw = blockDim.x / WAVE, passes = (end - begin + WAVE - 1) / WAVE;   // none for an empty tile
-    for (int jr = threadIdx.x / WAVE; jr < passes; jr += nw) {
+    const int passes = (end - begin + WAVE - 1) / WAVE;   // none for an empty tile
+    const int nw = a.split * (BLOCK / WAVE);
+    for (int jr = part * (BLOCK / WAVE) + threadIdx.x / WAVE; jr < passes; jr += nw) {
         const int i = begin + jr * WAVE + lane_id();
         const bool live = i < end;
         const int ii = live ? i : begin;
@@ -1410,6 +1495,7 @@ struct RotArgs {
     const double *bz, *az, *g1, *g2;
     int M1, M2, TW;
     double dt;
+    int split;   // blocks per tile
 };
 
 template <int P, bool SPIN>
@@ -1417,7 +1503,8 @@ __global__ __launch_bounds__(BLOCK) void k2_rotate_tiles(RotArgs a) {
     constexpr int PR = P + 1, PCM = TWMAX + P, PS = PR * PCM;
     __shared__ double sA[PS], sB[PS], sG1[SPIN ? PS : 1], sG2[SPIN ? PS : 1];
     const int nseg = a.M2 / a.TW;
-    const int tile = tile_of_block();
+    int part;
+    const int tile = tile_of_block(a.split, part);
     const int r = tile / nseg, c0 = (tile - r * nseg) * a.TW;
     const int PC = a.TW + P;
     const int R0 = r - P, C0 = c0 - P;
@@ -1433,7 +1520,7 @@ __global__ __launch_bounds__(BLOCK) void k2_rotate_tiles(RotArgs a) {
     }
     __syncthreads();
     const int begin = a.start[tile], end = a.start[tile + 1];
-    for (int i = begin + threadIdx.x; i < end; i += blockDim.x) {
+    for (int i = begin + part * BLOCK + threadIdx.x; i < end; i += a.split * BLOCK) {
         const double u1 = a.xi1[i], u2 = a.xi2[i];
         const int c2 = (int)u2;
         const double t1 = u1 - r, t2 = u2 - c2;
@@ -1567,23 +1654,38 @@ __global__ __launch_bounds__(BLOCK) void k2_gauss(const double *__restrict__ u1,
     block_max_to(m, res);
 }
 
-// End of one fixed-point iteration (unless an earlier one converged): its
-// residuals ra, rb (rb may be null) and the status flags (may be null) go to
-// the host mirror h[0..2], and the gate closes when a flag is set, a residual
-// is not finite, or the larger one is at most tol: the conditions on which the
-// host stops at this iteration.
-__global__ void k2_check(const unsigned long long *ra, const unsigned long long *rb, const int *flags, double tol,
-                         int *gate, double *h) {
-    if (*gate) return;
-    double a, b = 0.0;
-    const unsigned long long ba = *ra, bb = rb ? *rb : 0ull;
-    memcpy(&a, &ba, sizeof(a));
-    memcpy(&b, &bb, sizeof(b));
-    const int f = flags ? *flags : 0;
-    h[0] = a;
-    h[1] = b;
-    h[2] = (double)f;
-    if (f || !isfinite(a) || !isfinite(b) || fmax(a, b) <= tol) *gate = 1;
+// End of one fixed-point iteration, run by the last block of its solve: the
+// larger of the residuals ra, rb (rb may be null; +inf if one is not finite), or
+// -2 - flags if a status flag is set (flags may be null), goes to the iteration's
+// word of the host mirror, and the gate closes when a flag is set, a residual is
+// not finite, or the larger one is at most tol: the conditions on which the host
+// stops at this iteration.
+struct IterEnd {
+    const unsigned long long *ra, *rb;
+    const int *flags;
+    double tol;
+    int *gate;
+    double *h;        // null: the solve ends no iteration
+    unsigned *done;   // blocks finished (zero between solves)
+};
+
+// Called by thread 0 of every block once it has recorded the block's residual by an
+// atomic.  Only atomics are exchanged here, so waiting for them is enough: a fence
+// would write every block's field values back from L2 (3 to 4 us per solve), which
+// the next kernel's start does anyway.
+__device__ __forceinline__ void end_iteration(const IterEnd &e) {
+    wait_memory();
+    if (atomicAdd(e.done, 1u) != gridDim.x - 1) return;
+    wait_memory();
+    auto load = [](const unsigned long long *p) {
+        return __longlong_as_double((long long)__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    };
+    const double a = load(e.ra), b = e.rb ? load(e.rb) : 0.0;
+    const int f = e.flags ? __hip_atomic_load(e.flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    const double r = isfinite(a) && isfinite(b) ? fmax(a, b) : HUGE_VAL;
+    *e.done = 0u;
+    if (f || !(r > e.tol) || !isfinite(r)) *e.gate = 1;
+    *const_cast<volatile double *>(e.h) = f ? -2.0 - f : r;
 }
 
 // ---------------------------------------------------------------------------
@@ -1721,9 +1823,10 @@ __global__ __launch_bounds__(BLOCK) void k2_fft_rows_fwd(Ptrs<NB> src, int zero_
     const bool zero = (zero_mask >> b) & 1;
     double2 x[8];
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
-        x[m] = make_double2(act ? s[t + m * T] : 0.0, 0.0);
-        if (act && zero) s[t + m * T] = 0.0;
+    for (int m = 0; m < 8; ++m) x[m] = make_double2(act ? s[t + m * T] : 0.0, 0.0);
+    if (act && zero) {
+#pragma unroll
+        for (int m = 0; m < 8; ++m) s[t + m * T] = 0.0;
     }
     __syncthreads();
     fft8<false>(x, t, n, lds, 1, fl * n, stw);
@@ -1797,7 +1900,7 @@ __global__ __launch_bounds__(BLOCK) void k2_fft_cols(double2 *__restrict__ Z, in
 template <int NB, class Epi>
 __global__ __launch_bounds__(BLOCK) void k2_fft_rows_inv(const double2 *__restrict__ Z, int M1, int M2,
                                                          const double2 *__restrict__ tw2, double invN, Epi epi,
-                                                         const int *gate) {
+                                                         const int *gate, IterEnd end) {
     if (gate && *gate) return;   // uniform over the grid
     __shared__ double2 lds[8 * BLOCK], stw[MAXM / 2];
     const int n = M2, T = n >> 3, per = BLOCK / T;
@@ -1813,38 +1916,276 @@ __global__ __launch_bounds__(BLOCK) void k2_fft_rows_inv(const double2 *__restri
     fft8<true>(x, t, n, lds, 1, fl * n, stw);
     double mx = 0.0;
     if (act) {
+        typename Epi::In in[8];   // every load issued before the first store
 #pragma unroll
-        for (int m = 0; m < 8; ++m) mx = fmax(mx, epi(b, row * M2 + t + m * T, x[m].x * invN));
+        for (int m = 0; m < 8; ++m) in[m] = epi.load(b, row * M2 + t + m * T);
+#pragma unroll
+        for (int m = 0; m < 8; ++m) mx = fmax(mx, epi(b, row * M2 + t + m * T, x[m].x * invN, in[m]));
     }
     if (epi.res) block_max_to(mx, epi.res);
+    if (end.h && threadIdx.x == 0) end_iteration(end);
+}
+
+// The whole solve of one grid in one block, for grids of at most SMALL_SOLVE
+// nodes and operators that act on each grid by itself (op.one): the transform
+// along x2, along x1, the spectral step, and both back, the values in registers (8
+// per thread) and exchanged through LDS, one block per grid.  Against the three
+// kernels (events): 16 x 16 nodes 14.0 and 18.9 us, 32 x 64 17.3 and 20.2, 64 x 64
+// 22.5 and 21.3.
+constexpr int SMALL_SOLVE = 2048;
+
+inline size_t small_solve_lds(int M1, int M2) {
+    return sizeof(double2) * ((size_t)std::max(M1 * M2, 8 * WAVE) + M1 / 2 + M2 / 2);
+}
+
+template <int NB, class Op, class Epi>
+__global__ __launch_bounds__(SMALL_SOLVE / 8) void k2_solve_small(Ptrs<NB> src, int M1, int M2,
+                                                                  const double2 *__restrict__ tw1,
+                                                                  const double2 *__restrict__ tw2, double invN, Op op,
+                                                                  Epi epi, const int *gate, IterEnd end) {
+    if (gate && *gate) return;   // uniform over the grid
+    extern __shared__ double2 small_lds[];
+    const int N = M1 * M2, b = blockIdx.x, tid = threadIdx.x;
+    double2 *lds = small_lds, *st1 = lds + max(N, 8 * WAVE), *st2 = st1 + M1 / 2;
+    double *s = src.p[0];
+#pragma unroll
+    for (int q = 1; q < NB; ++q)
+        if (b == q) s = src.p[q];
+    for (int i = tid; i < M1 / 2; i += blockDim.x) st1[i] = tw1[i];
+    for (int i = tid; i < M2 / 2; i += blockDim.x) st2[i] = tw2[i];
+    const bool act = tid < N / 8;   // a block has at least one wave; idle threads have LDS of their own
+    const int T2 = M2 >> 3, row = tid / T2, t2 = tid - row * T2;
+    const int T1 = M1 >> 3, t1 = tid / M2, col = tid - t1 * M2;
+    const int base2 = row * M2, o2 = base2 + t2;
+    double2 x[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) x[m] = make_double2(act ? s[o2 + m * T2] : 0.0, 0.0);
+    if (act) {   // the accumulator of the next deposit
+#pragma unroll
+        for (int m = 0; m < 8; ++m) s[o2 + m * T2] = 0.0;
+    }
+    __syncthreads();
+    fft8<false>(x, t2, M2, lds, 1, base2, st2);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) lds[o2 + m * T2] = x[m];
+    __syncthreads();
+    // idle threads (grids under 512 nodes) read and write behind the grid's columns
+    const int c1 = act ? col : N + tid, sp = act ? M2 : 0;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) x[m] = lds[c1 + (t1 + m * T1) * sp];
+    __syncthreads();
+    fft8<false>(x, t1, M1, lds, sp, c1, st1);
+    if (act) {
+#pragma unroll
+        for (int m = 0; m < 8; ++m) x[m] = op.one(b, t1 + m * T1, col, x[m]);
+    }
+    fft8<true>(x, t1, M1, lds, sp, c1, st1);
+    if (act) {
+#pragma unroll
+        for (int m = 0; m < 8; ++m) lds[c1 + (t1 + m * T1) * sp] = x[m];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) x[m] = lds[o2 + m * T2];
+    __syncthreads();
+    fft8<true>(x, t2, M2, lds, 1, base2, st2);
+    double mx = 0.0;
+    if (act) {
+        typename Epi::In in[8];
+#pragma unroll
+        for (int m = 0; m < 8; ++m) in[m] = epi.load(b, o2 + m * T2);
+#pragma unroll
+        for (int m = 0; m < 8; ++m) mx = fmax(mx, epi(b, o2 + m * T2, x[m].x * invN, in[m]));
+    }
+    block_max_to(mx, epi.res);
+    if (tid == 0) end_iteration(end);
 }
 
 // ---- spectral steps -------------------------------------------------------
-// M1^{-1} on the current (Subsystem I): component 1 has symbol m1(t1) m0(t2),
-// component 2 m0(t1) m1(t2).
-struct OpM1inv {
-    static constexpr bool INVERSE = true;
-    Sym s;
-    __device__ void operator()(int k1, int k2, double2 (&v)[2]) const {
-        const double d1 = 1.0 / (s.m1a[k1] * s.m0b[k2]), d2 = 1.0 / (s.m0a[k1] * s.m1b[k2]);
-        v[0].x *= d1; v[0].y *= d1;
-        v[1].x *= d2; v[1].y *= d2;
-    }
+// M1 is a tensor product on each component, so its inverse is one circulant
+// convolution along x2 and one along x1, with the first rows of the 1D inverses.
+// Those decay geometrically (99 entries above 1e-18 for the quadratic mass matrix, 133
+// for the cubic, about 240 for the quintic) and wrap around a grid that is shorter.
+// A thread forms 8 neighbouring outputs from a sliding window: 64 FMAs per 8 LDS
+// reads, the weights in scalar registers.
+struct ConvTaps {           // one direction, per component
+    const double *rt[2];    // the row's entries in reverse, zeros on both sides
+    int nt[2], hi[2];       // entries; offset of the first one
 };
 
+__host__ __device__ constexpr int conv_steps(int nt) { return (nt + 14) & ~7; }
+
+// acc[j] = sum_q rt[q] x(q + j), q = 0 .. nt - 1, j < 8: output 8 t + j of the
+// convolution when x(s) is the input at 8 t - hi + s.
+template <class X>
+__device__ __forceinline__ void conv8(double (&acc)[8], const double *__restrict__ rt, int nt, X x) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] = 0.0;
+    for (int s0 = 0; s0 < conv_steps(nt); s0 += 8) {
+        double v[8], w[15];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) v[r] = x(s0 + r);
+#pragma unroll
+        for (int k = 0; k < 15; ++k) w[k] = rt[s0 - 7 + k];
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] = fma(w[7 + r - j], v[r], acc[j]);
+    }
+}
+
+// LDS place of position i of a row: consecutive threads are 8 positions apart, the
+// padding spreads them over the banks.
+__device__ __forceinline__ int conv_pad(int i) { return i + (i >> 3); }
+
+// Along x2: T = (1D inverse) J row by row, M2 / 8 threads each; J is zeroed (the
+// accumulators of the next deposit).
+__global__ __launch_bounds__(BLOCK) void k2_conv_rows(Ptrs<2> src, double *__restrict__ T, int M1, int M2, ConvTaps tp,
+                                                      const int *gate) {
+    if (gate && *gate) return;   // uniform over the grid
+    __shared__ double lds[9 * BLOCK];
+    const int T2 = M2 >> 3, per = BLOCK / T2;
+    const int fl = threadIdx.x / T2, t = threadIdx.x - fl * T2;
+    const int blocks = (M1 + per - 1) / per, b = blockIdx.x / blocks;   // component
+    const int row = (blockIdx.x - b * blocks) * per + fl;
+    const bool act = row < M1;
+    double *s = (b ? src.p[1] : src.p[0]) + (size_t)row * M2;
+    double *x = lds + fl * 9 * T2;
+    double in[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) in[m] = act ? s[t + m * T2] : 0.0;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        x[conv_pad(t + m * T2)] = in[m];
+        if (act) s[t + m * T2] = 0.0;
+    }
+    __syncthreads();
+    const double *rt = b ? tp.rt[1] : tp.rt[0];
+    const int nt = b ? tp.nt[1] : tp.nt[0], first = 8 * t - (b ? tp.hi[1] : tp.hi[0]), mask = M2 - 1;
+    double acc[8];
+    conv8(acc, rt, nt, [&](int q) { return x[conv_pad((first + q) & mask)]; });
+    if (act) {
+        double2 *o = reinterpret_cast<double2 *>(T + (size_t)b * M1 * M2 + (size_t)row * M2 + 8 * t);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = make_double2(acc[2 * j], acc[2 * j + 1]);
+    }
+}
+
+// Along x1: a block forms TR rows (64, or M1 if it is less) of BLOCK 8 / TR columns,
+// its input rows in LDS (lanes of a wave on consecutive columns); entry g of
+// component b goes to epi(b, g, v).
+template <class Epi>
+__global__ __launch_bounds__(BLOCK) void k2_conv_cols(const double *__restrict__ T, int M1, int M2, int TR, ConvTaps tp,
+                                                      Epi epi, const int *gate, IterEnd end) {
+    if (gate && *gate) return;   // uniform over the grid
+    extern __shared__ double conv_lds[];
+    const int CB = 8 * BLOCK / TR, cblocks = (M2 + CB - 1) / CB, rblocks = M1 / TR;
+    const int b = blockIdx.x / (cblocks * rblocks), q = blockIdx.x - b * cblocks * rblocks;
+    const int r0 = (q / cblocks) * TR, c0 = (q % cblocks) * CB;
+    const double *rt = b ? tp.rt[1] : tp.rt[0];
+    const int nt = b ? tp.nt[1] : tp.nt[0], hi = b ? tp.hi[1] : tp.hi[0];
+    const int H = TR - 8 + conv_steps(nt);   // input rows r0 - hi .. r0 - hi + H - 1
+    const int col = threadIdx.x % CB, t = threadIdx.x / CB;
+    const bool act = c0 + col < M2;
+    const double *src = T + (size_t)b * M1 * M2 + min(c0 + col, M2 - 1);
+    const int step = BLOCK / CB;
+    for (int h0 = t; h0 < H; h0 += 8 * step) {   // 8 loads in flight
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = src[(size_t)((r0 - hi + min(h0 + k * step, H - 1)) & (M1 - 1)) * M2];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (h0 + k * step < H) conv_lds[(h0 + k * step) * CB + col] = v[k];
+    }
+    __syncthreads();
+    double acc[8];
+    typename Epi::In in[8];   // in flight during the sums
+    const int g0 = (r0 + 8 * t) * M2 + min(c0 + col, M2 - 1);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) in[j] = epi.load(b, g0 + j * M2);
+    const double *x = conv_lds + 8 * t * CB + col;
+    conv8(acc, rt, nt, [&](int s) { return x[s * CB]; });
+    double mx = 0.0;
+    if (act) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) mx = fmax(mx, epi(b, g0 + j * M2, acc[j], in[j]));
+    }
+    block_max_to(mx, epi.res);
+    if (threadIdx.x == 0) end_iteration(end);
+}
+
+// Both directions in one block per component, for grids of at most CONV_SMALL nodes
+// (two FFT solves took 15.7 us at 16 x 16 nodes, this takes 10; 64 x 64 in 20 us, the
+// two kernels above 27 us at 128 x 128; 512 x 512: 35 us, by FFTs 48).
+constexpr int CONV_SMALL = 4096;
+
+template <class Epi>
+__global__ __launch_bounds__(CONV_SMALL / 8) void k2_conv_small(Ptrs<2> src, int M1, int M2, ConvTaps rows,
+                                                                ConvTaps cols, Epi epi, const int *gate, IterEnd end) {
+    if (gate && *gate) return;   // uniform over the grid
+    __shared__ double lds[CONV_SMALL / 8 * 9];
+    const int N = M1 * M2, b = blockIdx.x, tid = threadIdx.x;
+    const bool act = tid < N / 8;   // a block has at least one wave
+    double *s = b ? src.p[1] : src.p[0];
+    double acc[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) acc[m] = act ? s[tid + m * (N / 8)] : 0.0;
+    if (act) {
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            lds[conv_pad(tid + m * (N / 8))] = acc[m];
+            s[tid + m * (N / 8)] = 0.0;
+        }
+    }
+    __syncthreads();
+    {
+        const int T2 = M2 >> 3, row = tid / T2, t = tid - row * T2;
+        const double *x = lds + (act ? 9 * T2 * row : 0);
+        const int first = 8 * t - (b ? rows.hi[1] : rows.hi[0]), mask = M2 - 1;
+        conv8(acc, b ? rows.rt[1] : rows.rt[0], b ? rows.nt[1] : rows.nt[0],
+              [&](int q) { return x[conv_pad((first + q) & mask)]; });
+    }
+    __syncthreads();   // every input is read
+    if (act) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) lds[conv_pad(8 * tid + j)] = acc[j];
+    }
+    __syncthreads();
+    const int t = tid / M2, col = tid - t * M2;
+    {
+        const int first = 8 * t - (b ? cols.hi[1] : cols.hi[0]), mask = M1 - 1;
+        conv8(acc, b ? cols.rt[1] : cols.rt[0], b ? cols.nt[1] : cols.nt[0],
+              [&](int q) { return lds[conv_pad(((first + q) & mask) * M2 + col)]; });
+    }
+    double mx = 0.0;
+    if (act) {
+        typename Epi::In in[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) in[j] = epi.load(b, (8 * t + j) * M2 + col);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) mx = fmax(mx, epi(b, (8 * t + j) * M2 + col, acc[j], in[j]));
+    }
+    block_max_to(mx, epi.res);
+    if (tid == 0) end_iteration(end);
+}
+
 // e^{(k+1)} = e^n - M1^{-1} J; residual |e^{(k+1)} - e^{(k)}|; ebar = (e^n + e^{(k+1)})/2.
+// An epilogue's In holds the values it reads at an entry.
 struct EpiI {
     const double *en1, *en2;
     double *ek1, *ek2, *eb1, *eb2;
     unsigned long long *res;
-    __device__ double operator()(int b, int g, double v) const {
-        const double en = b ? en2[g] : en1[g];
+    struct In {
+        double en, ek;
+    };
+    __device__ In load(int b, int g) const { return b ? In{en2[g], ek2[g]} : In{en1[g], ek1[g]}; }
+    __device__ double operator()(int b, int g, double v, const In &in) const {
         double *ek = b ? ek2 : ek1;
         double *eb = b ? eb2 : eb1;
-        const double e = en - v;
-        const double d = fabs(e - ek[g]);
+        const double e = in.en - v;
+        const double d = fabs(e - in.ek);
         ek[g] = e;
-        eb[g] = 0.5 * (en + e);
+        eb[g] = 0.5 * (in.en + e);
         return isfinite(d) ? d : HUGE_VAL;   // a non-finite field shows in the residual
     }
 };
@@ -1891,18 +2232,23 @@ struct OpIII {
     const double2 *R;
     int M2;
     double dt;
-    __device__ void operator()(int k1, int k2, double2 (&v)[1]) const {
+    __device__ double2 one(int, int k1, int k2, double2 v) const {
         const double lam = s.m0a[k1] * s.m0b[k2] + 0.25 * dt * dt * kappa(s, k1, k2);
         const double2 r = R[(size_t)k1 * M2 + k2];
-        v[0] = make_double2((r.x + dt * v[0].x) / lam, (r.y + dt * v[0].y) / lam);
+        return make_double2((r.x + dt * v.x) / lam, (r.y + dt * v.y) / lam);
     }
+    __device__ void operator()(int k1, int k2, double2 (&v)[1]) const { v[0] = one(0, k1, k2, v[0]); }
 };
 
 struct EpiIII {
     double *ezk;
     unsigned long long *res;
-    __device__ double operator()(int, int g, double v) const {
-        const double d = fabs(v - ezk[g]);
+    struct In {
+        double ek;
+    };
+    __device__ In load(int, int g) const { return In{ezk[g]}; }
+    __device__ double operator()(int, int g, double v, const In &in) const {
+        const double d = fabs(v - in.ek);
         ezk[g] = v;
         return isfinite(d) ? d : HUGE_VAL;   // a non-finite field shows in the residual
     }
@@ -1975,7 +2321,9 @@ template <int NB>
 struct EpiStore {
     Ptrs<NB> out;
     unsigned long long *res;
-    __device__ double operator()(int b, int g, double v) const {
+    struct In {};
+    __device__ In load(int, int) const { return In{}; }
+    __device__ double operator()(int b, int g, double v, const In &) const {
 #pragma unroll
         for (int q = 0; q < NB; ++q)
             if (b == q && out.p[q]) out.p[q][g] = v;
@@ -2039,24 +2387,26 @@ struct ecpic2d_ctx {
     int32_t *cell = nullptr /* new cell (set_particles) or packed new tile and column (commit) */, *count = nullptr,
             *start = nullptr, *bsum = nullptr;
     int32_t *mig = nullptr;   // arrivals per new tile, after the stayers' slots
-    int32_t *tstart[2] = {}, *tstay = nullptr, *tarr = nullptr, *tcnt = nullptr;
+    int32_t *tstart[2] = {}, *tstay = nullptr, *tarr = nullptr;
     int ts = 0, ntiles = 0;   // tstart[ts]: first particle of each tile
     double *e1 = nullptr, *e2 = nullptr, *bz = nullptr, *ez = nullptr, *az = nullptr;
-    double *en1 = nullptr, *en2 = nullptr, *ek1 = nullptr, *ek2 = nullptr, *eb1 = nullptr, *eb2 = nullptr;
+    double *ek1 = nullptr, *ek2 = nullptr, *eb1[2] = {}, *eb2[2] = {};   // iterate; mean field by parity
     double *J1 = nullptr, *J2 = nullptr, *g1a = nullptr, *g2a = nullptr, *ezn = nullptr, *ezk = nullptr,
            *S = nullptr, *tmp = nullptr;
     double2 *Z = nullptr, *R = nullptr, *tw1 = nullptr, *tw2 = nullptr;
+    ConvTaps conv_a{}, conv_b{};  // M1^{-1} along x1 and x2
     double *sym = nullptr;        // m0a m1a cra cia (M1 each) m0b m1b crb cib (M2 each)
     double *partial = nullptr;    // RED_BLOCKS + 8
     unsigned long long *res = nullptr;   // 3 * MAXK + 4 slots
     int *flags = nullptr;
-    int *gate = nullptr;                 // set once an iteration has converged (or failed)
+    int *gate = nullptr;                 // [0] set once an iteration has converged (or failed), [1] never
     int spin = 0;                        // particles carry spins (hbar terms on)
     double hbar = 0.0;
     double *sx[2] = {}, *sy[2] = {}, *sz[2] = {};   // spins, in the particle buffers' order
     double *Dx = nullptr, *Dy = nullptr, *Dz = nullptr, *ssrc = nullptr;   // spin deposits and G*^T source
-    double *hres = nullptr, *hres_dev = nullptr;   // pinned mirror: 3 values per iteration (I, then III)
-    hipEvent_t ev[2] = {};
+    double *hres = nullptr, *hres_dev = nullptr;   // pinned mirror: a word per iteration (I, then III)
+    unsigned *done = nullptr;            // blocks finished of the solve that ends an iteration
+    int keep_from = 0, last_k = 0;       // first sweep that stores its momentum; last sweep of the last substep
     bool have_particles = false;
     std::vector<double> m0row, m1row;
     Prof2 prof;
@@ -2118,6 +2468,17 @@ Sym sym_of(ecpic2d_ctx *c) {
 
 int n_tiles(ecpic2d_ctx *c) { return c->M1 * (c->M2 / c->TW); }
 
+// Blocks per tile of the particle passes: enough that the launch has about 1024
+// blocks (the chip holds 512 to 1536 of them), as long as every wave keeps a row of
+// 64 particles on average.  Each block stages its own patch and adds its own deposits
+// to the grid, so more blocks than that cost: 128 tiles (128 x 64 cells, 5e5 quintic
+// particles) sweep 112 -> 79 us, III deposit 45 -> 27 us with 8 blocks each; 1024
+// tiles (256 x 256, 2^22 with spin) sweep 180 us with one block, 194 with two.
+int blocks_per_tile(ecpic2d_ctx *c) {
+    const int64_t nt = n_tiles(c), rows = c->N / nt / BLOCK;   // rows of a tile per wave of one block
+    return (int)std::max<int64_t>(1, std::min<int64_t>(1024 / nt, rows));
+}
+
 // Full cell sort (set_particles): counts in c->count, cells in c->cell; each tile
 // is stored transposed (tile_pos), and the tile starts are taken from the cell starts.
 void sort_particles(ecpic2d_ctx *c) {
@@ -2146,11 +2507,8 @@ int2 *leavers_of(ecpic2d_ctx *c, int di) { return reinterpret_cast<int2 *>(c->d1
 void sort_tiles(ecpic2d_ctx *c, int di) {
     const int A = c->cur, B = 1 - c->cur, T0 = c->ts, T1 = 1 - c->ts;
     timed(c, "sort", [&] {
-        const int nt = c->ntiles, nb = (nt + SCAN_TILE - 1) / SCAN_TILE;
-        k2_tile_counts<<<grid_for(nt), BLOCK, 0, c->stream>>>(c->tstay, c->tarr, c->tcnt, nt);
-        k2_scan_sums<<<nb, SCAN_THREADS, 0, c->stream>>>(c->tcnt, c->bsum, nt);
-        k2_scan_top<<<1, SCAN_THREADS, 0, c->stream>>>(c->bsum, nb, c->tstart[T1] + nt);
-        k2_scan_apply<<<nb, SCAN_THREADS, 0, c->stream>>>(c->tcnt, c->tstart[T1], c->bsum, nt);
+        const int nt = c->ntiles;
+        k2_scan_tiles<<<1, SCAN_THREADS, 0, c->stream>>>(c->tstay, c->tarr, c->tstart[T1], nt);
         k2_list_arrivals<<<nt, WAVE, 0, c->stream>>>(c->cell, leavers_of(c, di), c->tstart[T0], c->tstart[T1],
                                                     c->tstay, c->mig);
         const Resort r{c->xi1[A], c->xi2[A], c->d1[di], c->d2[di], c->pk1, c->pk2, c->id[A], c->cell, c->mig,
@@ -2163,10 +2521,11 @@ void sort_tiles(ecpic2d_ctx *c, int di) {
     c->ts = T1;
 }
 
-// Forward rows -> columns with op -> inverse rows with epi, over NB grids.
+// Forward rows -> columns with op -> inverse rows with epi, over NB grids; with
+// `end` the solve ends an iteration.
 template <int NB, class Op, class Epi>
 void spectral(ecpic2d_ctx *c, const char *name, Ptrs<NB> src, int zero_mask, Op op, Epi epi,
-              const int *gate = nullptr) {
+              const int *gate = nullptr, IterEnd end = {}) {
     timed(c, name, [&] {
         // transforms per block: BLOCK / (n / 8) for n points
         const int rows = NB * c->M1, per_row = BLOCK / (c->M2 / 8), per_col = BLOCK / (c->M1 / 8);
@@ -2175,17 +2534,67 @@ void spectral(ecpic2d_ctx *c, const char *name, Ptrs<NB> src, int zero_mask, Op 
         k2_fft_cols<NB, Op><<<gcol, BLOCK, 0, c->stream>>>(c->Z, c->M1, c->M2, c->tw1, op, gate);
         if (Op::INVERSE)
             k2_fft_rows_inv<NB, Epi><<<grow, BLOCK, 0, c->stream>>>(c->Z, c->M1, c->M2, c->tw2, 1.0 / (double)c->Nc,
-                                                                  epi, gate);
+                                                                  epi, gate, end);
     });
 }
 
-// Host view of one iteration's mirror (residuals h[0], h[1], flags h[2]).
-int status_of(const double *h) {
-    const int f = (int)h[2];
-    if (f & FLAG_NONFINITE) return ECPIC_ENONFINITE;
-    if (f & FLAG_CFL) return ECPIC_ECFL;
-    if (!std::isfinite(h[0]) || !std::isfinite(h[1])) return ECPIC_ENONFINITE;
-    return ECPIC_OK;
+// The Subsystem III solve that ends an iteration (S is zeroed after it is read): one
+// block where the grid fits, else the three kernels.
+template <class Op, class Epi>
+void solve_iteration(ecpic2d_ctx *c, const char *name, double *S, Op op, Epi epi, IterEnd end) {
+    if (c->Nc > SMALL_SOLVE) {
+        spectral<1>(c, name, Ptrs<1>{{S}}, 1, op, epi, c->gate, end);
+        return;
+    }
+    timed(c, name, [&] {
+        k2_solve_small<1, Op, Epi><<<1, std::max(WAVE, c->Nc / 8), small_solve_lds(c->M1, c->M2), c->stream>>>(
+            Ptrs<1>{{S}}, c->M1, c->M2, c->tw1, c->tw2, 1.0 / (double)c->Nc, op, epi, c->gate, end);
+    });
+}
+
+// M1^{-1} of the current with epi: the convolutions in one kernel where the grid fits,
+// else one per direction.
+template <class Epi>
+void solve_M1(ecpic2d_ctx *c, const char *name, Epi epi, IterEnd end) {
+    const Ptrs<2> J{{c->J1, c->J2}};
+    timed(c, name, [&] {
+        if (c->Nc <= CONV_SMALL) {
+            k2_conv_small<Epi><<<2, std::max(WAVE, c->Nc / 8), 0, c->stream>>>(J, c->M1, c->M2, c->conv_b, c->conv_a, epi,
+                                                                            c->gate, end);
+            return;
+        }
+        const int per = BLOCK / (c->M2 / 8), TR = std::min(64, c->M1), CB = 8 * BLOCK / TR;
+        double *T = reinterpret_cast<double *>(c->Z);
+        k2_conv_rows<<<2 * ((c->M1 + per - 1) / per), BLOCK, 0, c->stream>>>(J, T, c->M1, c->M2, c->conv_b, c->gate);
+        const int nt = std::max(c->conv_a.nt[0], c->conv_a.nt[1]);
+        const size_t lds = sizeof(double) * (size_t)CB * (TR - 8 + conv_steps(nt));
+        k2_conv_cols<Epi><<<2 * (c->M1 / TR) * ((c->M2 + CB - 1) / CB), BLOCK, lds, c->stream>>>(
+            T, c->M1, c->M2, TR, c->conv_a, epi, c->gate, end);
+    });
+}
+
+// Wait until the iteration with the mirror word h is done: the last block of its
+// solve writes it (it is set to MIRROR_WAIT when the iteration is queued).  Ends
+// also if the stream runs dry or fails without it.  r gets the residual.
+constexpr double MIRROR_WAIT = -1.0;
+
+int wait_mirror(ecpic2d_ctx *c, const double *h, double &r) {
+    const volatile double *flag = h;
+    for (unsigned n = 1;; ++n) {
+        if (*flag != MIRROR_WAIT) break;
+        if (n % 4096 == 0) {
+            const hipError_t e = hipStreamQuery(c->stream);
+            if (hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();   // no error
+            if (e == hipErrorNotReady) continue;
+            if (e != hipSuccess || *flag == MIRROR_WAIT) return ECPIC_EDEVICE;
+        }
+    }
+    r = *flag;
+    if (r < 0.0) {
+        const int f = (int)(-2.0 - r);
+        return (f & FLAG_NONFINITE) ? ECPIC_ENONFINITE : ECPIC_ECFL;
+    }
+    return std::isfinite(r) ? ECPIC_OK : ECPIC_ENONFINITE;
 }
 
 int flags_status(ecpic2d_ctx *c) {
@@ -2219,46 +2628,44 @@ double read_res(ecpic2d_ctx *c, int slot, int *rc) {
     }
 
 int substep_I(ecpic2d_ctx *c, double dt, ecpic2d_iter_stats *st) {
-    const int A = c->cur, Nc = c->Nc, gC = grid_for(Nc);
+    const int A = c->cur, Nc = c->Nc;
     hipStream_t s = c->stream;
-    k2_fill_u64<<<1, 2 * MAXK, 0, s>>>(c->res, 2 * MAXK);
-    k2_fill_i32<<<1, 1, 0, s>>>(c->flags, 1);
-    k2_grad<<<gC, BLOCK, 0, s>>>(c->az, c->g1a, c->g2a, c->M1, c->M2, 1.0 / c->dx1, 1.0 / c->dx2);
-    k2_copy<<<gC, BLOCK, 0, s>>>(c->en1, c->e1, Nc);
-    k2_copy<<<gC, BLOCK, 0, s>>>(c->en2, c->e2, Nc);
-    k2_copy<<<gC, BLOCK, 0, s>>>(c->ek1, c->e1, Nc);
-    k2_copy<<<gC, BLOCK, 0, s>>>(c->ek2, c->e2, Nc);
-    k2_copy<<<gC, BLOCK, 0, s>>>(c->eb1, c->e1, Nc);
-    k2_copy<<<gC, BLOCK, 0, s>>>(c->eb2, c->e2, Nc);
-    k2_fill<<<gC, BLOCK, 0, s>>>(c->J1, Nc, 0.0);
-    k2_fill<<<gC, BLOCK, 0, s>>>(c->J2, Nc, 0.0);
-    k2_fill_i32<<<1, 1, 0, s>>>(c->gate, 1);
-    const Sym sy = sym_of(c);
-    // Sweep k reads d^(k) from buffer k & 1 and writes d^(k+1) to the other;
-    // then the field update, the check, and event ev[k & 1].
-    auto iterate = [&](int k) {
+    k2_begin_I<<<grid_for(Nc), BLOCK, 0, s>>>(BeginI{c->az, c->e1, c->e2, c->g1a, c->g2a, c->ek1, c->ek2, c->eb1[0],
+                                                     c->eb2[0], c->J1, c->J2, c->res, 2 * MAXK, c->flags, c->gate,
+                                                     c->M1, c->M2, 1.0 / c->dx1, 1.0 / c->dx2});
+    const int split = blocks_per_tile(c);
+    // Sweep k reads d^(k) and the mean field from buffers k & 1 and writes d^(k+1)
+    // to the other.
+    auto sweep = [&](int k, bool keep_p, const int *gate) {
         const int di = k & 1;
         SweepArgs a{c->xi1[A], c->xi2[A], c->p1[A], c->p2[A], c->d1[di], c->d2[di], c->d1[1 - di], c->d2[1 - di],
-                    c->pk1, c->pk2, c->tstart[c->ts], c->eb1, c->eb2, c->az, c->g1a, c->g2a, c->J1, c->J2,
-                    c->res + k, c->flags, c->gate, c->M1, c->M2, c->TW, 1.0 / c->dx1, 1.0 / c->dx2, dt, c->w,
-                    c->sx[A], c->sy[A], c->sz[A], c->bz, c->hbar, c->azn, c->gamn};
+                    c->pk1, c->pk2, c->tstart[c->ts], c->eb1[di], c->eb2[di], c->az, c->g1a, c->g2a, c->J1, c->J2,
+                    c->res + k, c->flags, gate, c->M1, c->M2, c->TW, 1.0 / c->dx1, 1.0 / c->dx2, dt, c->w,
+                    c->sx[A], c->sy[A], c->sz[A], c->bz, c->hbar, c->azn, c->gamn, keep_p ? 1 : 0, split};
         timed(c, "sweep_I", [&] {
             if (c->spin) {
                 if (k == 0) {
-                    LAUNCH_P(c->P, k2_sweep_I<PP, true, true><<<n_tiles(c), BLOCK, 0, s>>>(a));
+                    LAUNCH_P(c->P, k2_sweep_I<PP, true, true><<<n_tiles(c) * split, BLOCK, 0, s>>>(a));
                 } else {
-                    LAUNCH_P(c->P, k2_sweep_I<PP, false, true><<<n_tiles(c), BLOCK, 0, s>>>(a));
+                    LAUNCH_P(c->P, k2_sweep_I<PP, false, true><<<n_tiles(c) * split, BLOCK, 0, s>>>(a));
                 }
             } else if (k == 0) {
-                LAUNCH_P(c->P, k2_sweep_I<PP, true, false><<<n_tiles(c), BLOCK, 0, s>>>(a));
+                LAUNCH_P(c->P, k2_sweep_I<PP, true, false><<<n_tiles(c) * split, BLOCK, 0, s>>>(a));
             } else {
-                LAUNCH_P(c->P, k2_sweep_I<PP, false, false><<<n_tiles(c), BLOCK, 0, s>>>(a));
+                LAUNCH_P(c->P, k2_sweep_I<PP, false, false><<<n_tiles(c) * split, BLOCK, 0, s>>>(a));
             }
         });
-        spectral<2>(c, "solve_I", Ptrs<2>{{c->J1, c->J2}}, 3, OpM1inv{sy},
-                    EpiI{c->en1, c->en2, c->ek1, c->ek2, c->eb1, c->eb2, c->res + MAXK + k}, c->gate);
-        k2_check<<<1, 1, 0, s>>>(c->res + k, c->res + MAXK + k, c->flags, c->tol, c->gate, c->hres_dev + 3 * k);
-        hipEventRecord(c->ev[k & 1], s);
+    };
+    // Only the committed sweep's momentum is wanted, so sweeps store theirs from the
+    // index on at which the last two substeps ended (16 of a sweep's 96 B per
+    // particle); a substep that ends earlier repeats its last sweep with the store.
+    auto iterate = [&](int k) {
+        const int di = k & 1;
+        c->hres[k] = MIRROR_WAIT;
+        sweep(k, k >= c->keep_from, c->gate);
+        solve_M1(c, "solve_I",
+                 EpiI{c->e1, c->e2, c->ek1, c->ek2, c->eb1[1 - di], c->eb2[1 - di], c->res + MAXK + k},
+                 IterEnd{c->res + k, c->res + MAXK + k, c->flags, c->tol, c->gate, c->hres_dev + k, c->done});
     };
     // Iteration k + 1 is queued before iteration k is read back, so the GPU
     // does not wait for the host; it does nothing if iteration k closed the gate.
@@ -2270,11 +2677,8 @@ int substep_I(ecpic2d_ctx *c, double dt, ecpic2d_iter_stats *st) {
     iterate(0);
     for (k = 0; k < c->kmax; ++k) {
         if (ahead && k + 1 < c->kmax) iterate(k + 1);
-        if (hipEventSynchronize(c->ev[k & 1]) != hipSuccess) return ECPIC_EDEVICE;
-        const double *h = c->hres + 3 * k;
-        rc = status_of(h);
+        rc = wait_mirror(c, c->hres + k, r);
         if (rc) break;
-        r = std::max(h[0], h[1]);
         if (r <= c->tol) break;
         if (!ahead && k + 1 < c->kmax) iterate(k + 1);
     }
@@ -2285,17 +2689,20 @@ int substep_I(ecpic2d_ctx *c, double dt, ecpic2d_iter_stats *st) {
     const int di = k & 1;
     if (st) { st->sweeps = std::min(k + 1, c->kmax); st->residual = r; st->reserved = 0; }
     if (k == c->kmax) return ECPIC_ENOTCONV;
-    // commit x^n + d^(k) (buffer di), p^(k+1), e^(k+1): new tiles and counts, the
+    if (k < c->keep_from) sweep(k, true, c->gate + 1);   // a gate that never closes
+    c->keep_from = std::min(k, c->last_k);
+    c->last_k = k;
+    // commit x^n + d^(k) (buffer di), p^(k+1), e^(k+1): places and counts, the
     // fields, then the re-sort writes the particles in their new order
     timed(c, "commit_I", [&] {
         k2_commit_tiles<<<c->ntiles, BLOCK, 0, s>>>(c->xi1[A], c->xi2[A], c->d1[di], c->d2[di], c->cell,
-                                                    leavers_of(c, di), c->tstart[c->ts], c->tstay, c->tarr, c->M1, c->M2, c->TW,
-                                                    1.0 / c->dx1, 1.0 / c->dx2);
+                                                    leavers_of(c, di), c->tstart[c->ts], c->tstay, c->tarr, c->M1,
+                                                    c->M2, c->TW, 1.0 / c->dx1, 1.0 / c->dx2);
     });
-    k2_copy<<<gC, BLOCK, 0, s>>>(c->e1, c->ek1, Nc);
-    k2_copy<<<gC, BLOCK, 0, s>>>(c->e2, c->ek2, Nc);
+    std::swap(c->e1, c->ek1);
+    std::swap(c->e2, c->ek2);
     sort_tiles(c, di);
-    return sync2(c);
+    return hipGetLastError() == hipSuccess ? ECPIC_OK : ECPIC_EDEVICE;
 }
 
 int substep_II(ecpic2d_ctx *c, double dt) {
@@ -2304,12 +2711,12 @@ int substep_II(ecpic2d_ctx *c, double dt) {
         k2_grad<<<grid_for(c->Nc), BLOCK, 0, c->stream>>>(c->az, c->g1a, c->g2a, c->M1, c->M2, 1.0 / c->dx1,
                                                           1.0 / c->dx2);
     const RotArgs a{c->xi1[A], c->xi2[A], c->p1[A], c->p2[A], c->sx[A], c->sy[A], c->sz[A], c->tstart[c->ts],
-                    c->bz, c->az, c->g1a, c->g2a, c->M1, c->M2, c->TW, dt};
+                    c->bz, c->az, c->g1a, c->g2a, c->M1, c->M2, c->TW, dt, blocks_per_tile(c)};
     timed(c, "rotate_II", [&] {
         if (c->spin) {
-            LAUNCH_P(c->P, k2_rotate_tiles<PP, true><<<n_tiles(c), BLOCK, 0, c->stream>>>(a));
+            LAUNCH_P(c->P, k2_rotate_tiles<PP, true><<<n_tiles(c) * a.split, BLOCK, 0, c->stream>>>(a));
         } else {
-            LAUNCH_P(c->P, k2_rotate_tiles<PP, false><<<n_tiles(c), BLOCK, 0, c->stream>>>(a));
+            LAUNCH_P(c->P, k2_rotate_tiles<PP, false><<<n_tiles(c) * a.split, BLOCK, 0, c->stream>>>(a));
         }
     });
     return ECPIC_OK;
@@ -2318,18 +2725,16 @@ int substep_II(ecpic2d_ctx *c, double dt) {
 int substep_III(ecpic2d_ctx *c, double dt, ecpic2d_iter_stats *st) {
     const int A = c->cur, Nc = c->Nc, gC = grid_for(Nc);
     hipStream_t s = c->stream;
-    k2_fill_u64<<<1, MAXK, 0, s>>>(c->res + 2 * MAXK, MAXK);
-    k2_copy<<<gC, BLOCK, 0, s>>>(c->ezn, c->ez, Nc);
-    k2_copy<<<gC, BLOCK, 0, s>>>(c->ezk, c->ez, Nc);
-    k2_fill<<<gC, BLOCK, 0, s>>>(c->S, Nc, 0.0);
+    k2_begin_III<<<gC, BLOCK, 0, s>>>(c->ez, c->ezn, c->ezk, c->S, Nc, c->res + 2 * MAXK, MAXK, c->gate);
     const Sym sy = sym_of(c);
+    const int split = blocks_per_tile(c);
     // constant part in Fourier space (with spin: plus dt hbar G*^T Lambda1*^T W S_xy)
     if (c->spin) {
         k2_fill<<<gC, BLOCK, 0, s>>>(c->Dx, Nc, 0.0);
         k2_fill<<<gC, BLOCK, 0, s>>>(c->Dy, Nc, 0.0);
-        LAUNCH_P(c->P, k2_deposit_spin<PP><<<n_tiles(c), BLOCK, 0, s>>>(c->xi1[A], c->xi2[A], c->sx[A], c->sy[A],
+        LAUNCH_P(c->P, k2_deposit_spin<PP><<<n_tiles(c) * split, BLOCK, 0, s>>>(c->xi1[A], c->xi2[A], c->sx[A], c->sy[A],
                                                                          c->sz[A], c->tstart[c->ts], c->Dx, c->Dy,
-                                                                         nullptr, c->M1, c->M2, c->TW, c->w, 0));
+                                                                         nullptr, c->M1, c->M2, c->TW, c->w, 0, split));
         k2_spin_src<<<gC, BLOCK, 0, s>>>(c->Dx, c->Dy, c->ssrc, c->M1, c->M2, 1.0 / c->dx1, 1.0 / c->dx2);
         spectral<3>(c, "solve_III", Ptrs<3>{{c->ezn, c->az, c->ssrc}}, 0, OpIIIrhsS{sy, c->R, c->M2, dt, c->hbar},
                     EpiStore<3>{Ptrs<3>{{nullptr, nullptr, nullptr}}, nullptr});
@@ -2337,16 +2742,14 @@ int substep_III(ecpic2d_ctx *c, double dt, ecpic2d_iter_stats *st) {
         spectral<2>(c, "solve_III", Ptrs<2>{{c->ezn, c->az}}, 0, OpIIIrhs{sy, c->R, c->M2, dt},
                     EpiStore<2>{Ptrs<2>{{nullptr, nullptr}}, nullptr});
     }
-    k2_fill_i32<<<1, 1, 0, s>>>(c->gate, 1);
-    auto iterate = [&](int k) {   // as in Subsystem I: deposit, solve, check, event ev[k & 1]
+    auto iterate = [&](int k) {   // as in Subsystem I
         DepArgs a{c->xi1[A], c->xi2[A], c->p1[A], c->p2[A], c->tstart[c->ts], c->az, c->ezn, c->ezk, c->S,
-                  c->pk1, c->M1, c->M2, c->TW, dt, c->w, 1, k == 0, c->gate};
-        timed(c, "deposit_III", [&] { LAUNCH_P(c->P, k2_deposit0<PP><<<n_tiles(c), BLOCK, 0, s>>>(a)); });
-        spectral<1>(c, "solve_III", Ptrs<1>{{c->S}}, 1, OpIII{sy, c->R, c->M2, dt},
-                    EpiIII{c->ezk, c->res + 2 * MAXK + k}, c->gate);
-        k2_check<<<1, 1, 0, s>>>(c->res + 2 * MAXK + k, nullptr, nullptr, c->tol, c->gate,
-                                 c->hres_dev + 3 * (MAXK + k));
-        hipEventRecord(c->ev[k & 1], s);
+                  c->pk1, c->M1, c->M2, c->TW, dt, c->w, 1, k == 0, c->gate, split};
+        c->hres[MAXK + k] = MIRROR_WAIT;
+        timed(c, "deposit_III", [&] { LAUNCH_P(c->P, k2_deposit0<PP><<<n_tiles(c) * split, BLOCK, 0, s>>>(a)); });
+        solve_iteration(c, "solve_III", c->S, OpIII{sy, c->R, c->M2, dt}, EpiIII{c->ezk, c->res + 2 * MAXK + k},
+                        IterEnd{c->res + 2 * MAXK + k, nullptr, nullptr, c->tol, c->gate, c->hres_dev + MAXK + k,
+                                c->done});
     };
     const bool ahead = !c->prof.on;
     double r = 0.0;
@@ -2354,11 +2757,8 @@ int substep_III(ecpic2d_ctx *c, double dt, ecpic2d_iter_stats *st) {
     iterate(0);
     for (k = 0; k < c->kmax; ++k) {
         if (ahead && k + 1 < c->kmax) iterate(k + 1);
-        if (hipEventSynchronize(c->ev[k & 1]) != hipSuccess) return ECPIC_EDEVICE;
-        const double *h = c->hres + 3 * (MAXK + k);
-        rc = status_of(h);
+        rc = wait_mirror(c, c->hres + MAXK + k, r);
         if (rc) break;
-        r = h[0];
         if (r <= c->tol) break;
         if (!ahead && k + 1 < c->kmax) iterate(k + 1);
     }
@@ -2376,9 +2776,10 @@ int substep_IV(ecpic2d_ctx *c, double dt) {
     if (c->spin) {   // with the constant source hbar C^T Lambda2^T W S_z
         const int A = c->cur;
         k2_fill<<<grid_for(c->Nc), BLOCK, 0, c->stream>>>(c->Dz, c->Nc, 0.0);
-        LAUNCH_P(c->P, k2_deposit_spin<PP><<<n_tiles(c), BLOCK, 0, c->stream>>>(
+        const int split = blocks_per_tile(c);
+        LAUNCH_P(c->P, k2_deposit_spin<PP><<<n_tiles(c) * split, BLOCK, 0, c->stream>>>(
                            c->xi1[A], c->xi2[A], c->sx[A], c->sy[A], c->sz[A], c->tstart[c->ts], nullptr, nullptr,
-                           c->Dz, c->M1, c->M2, c->TW, c->w, 1));
+                           c->Dz, c->M1, c->M2, c->TW, c->w, 1, split));
         spectral<4>(c, "maxwell_IV", Ptrs<4>{{c->e1, c->e2, c->bz, c->Dz}}, 0, OpIVs{sym_of(c), dt, c->hbar},
                     EpiStore<4>{Ptrs<4>{{c->e1, c->e2, c->bz, nullptr}}, nullptr});
         return ECPIC_OK;
@@ -2392,8 +2793,8 @@ void deposit_rho(ecpic2d_ctx *c, double *rho) {
     const int A = c->cur;
     k2_fill<<<grid_for(c->Nc), BLOCK, 0, c->stream>>>(rho, c->Nc, 0.0);
     DepArgs a{c->xi1[A], c->xi2[A], c->p1[A], c->p2[A], c->tstart[c->ts], nullptr, nullptr, nullptr, rho,
-              nullptr, c->M1, c->M2, c->TW, 0.0, c->w, 0, 0};
-    LAUNCH_P(c->P, k2_deposit0<PP><<<n_tiles(c), BLOCK, 0, c->stream>>>(a));
+              nullptr, c->M1, c->M2, c->TW, 0.0, c->w, 0, 0, nullptr, blocks_per_tile(c)};
+    LAUNCH_P(c->P, k2_deposit0<PP><<<n_tiles(c) * a.split, BLOCK, 0, c->stream>>>(a));
 }
 
 MassRows rows_of(ecpic2d_ctx *c, int d1, int d2) {
@@ -2468,10 +2869,9 @@ int ecpic2d_create(const ecpic2d_config *cfg, ecpic2d_ctx **out) {
           dalloc(c, &c->count, Nc) | dalloc(c, &c->start, Nc + 1) | dalloc(c, &c->bsum, Nc / SCAN_TILE + 2);
     c->ntiles = c->M1 * (c->M2 / c->TW);
     rc |= dalloc(c, &c->tstart[0], (size_t)c->ntiles + 1) | dalloc(c, &c->tstart[1], (size_t)c->ntiles + 1) |
-          dalloc(c, &c->tstay, (size_t)c->ntiles) | dalloc(c, &c->tarr, (size_t)c->ntiles) |
-          dalloc(c, &c->tcnt, (size_t)c->ntiles);
-    double **grids[] = {&c->e1, &c->e2, &c->bz, &c->ez, &c->az, &c->en1, &c->en2, &c->ek1, &c->ek2, &c->eb1,
-                        &c->eb2, &c->J1, &c->J2, &c->g1a, &c->g2a, &c->ezn, &c->ezk, &c->S, &c->tmp};
+          dalloc(c, &c->tstay, (size_t)c->ntiles) | dalloc(c, &c->tarr, (size_t)c->ntiles);
+    double **grids[] = {&c->e1, &c->e2, &c->bz, &c->ez, &c->az, &c->ek1, &c->ek2, &c->eb1[0],
+                        &c->eb1[1], &c->eb2[0], &c->eb2[1], &c->J1, &c->J2, &c->g1a, &c->g2a, &c->ezn, &c->ezk, &c->S, &c->tmp};
     for (double **gp : grids) rc |= dalloc(c, gp, Nc);
     if (c->spin) {
         for (int b = 0; b < 2; ++b) rc |= dalloc(c, &c->sx[b], N) | dalloc(c, &c->sy[b], N) | dalloc(c, &c->sz[b], N);
@@ -2480,14 +2880,12 @@ int ecpic2d_create(const ecpic2d_config *cfg, ecpic2d_ctx **out) {
     rc |= dalloc(c, &c->Z, 4 * Nc) | dalloc(c, &c->R, Nc) | dalloc(c, &c->tw1, (size_t)c->M1 / 2) |
           dalloc(c, &c->tw2, (size_t)c->M2 / 2) | dalloc(c, &c->sym, 4 * (size_t)(c->M1 + c->M2)) |
           dalloc(c, &c->partial, RED_BLOCKS + 16) | dalloc(c, &c->res, 3 * MAXK + 4) | dalloc(c, &c->flags, 1) |
-          dalloc(c, &c->gate, 1);
-    if (rc || hipHostMalloc((void **)&c->hres, sizeof(double) * 6 * MAXK, hipHostMallocMapped) != hipSuccess) {
+          dalloc(c, &c->gate, 2) | dalloc(c, &c->done, 1);
+    if (rc || hipHostMalloc((void **)&c->hres, sizeof(double) * 2 * MAXK, hipHostMallocMapped) != hipSuccess) {
         ecpic2d_destroy(c);
         return ECPIC_ENOMEM;
     }
-    if (hipHostGetDevicePointer((void **)&c->hres_dev, c->hres, 0) != hipSuccess ||
-        hipEventCreateWithFlags(&c->ev[0], hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&c->ev[1], hipEventDisableTiming) != hipSuccess) {
+    if (hipHostGetDevicePointer((void **)&c->hres_dev, c->hres, 0) != hipSuccess) {
         ecpic2d_destroy(c);
         return ECPIC_EDEVICE;
     }
@@ -2515,16 +2913,59 @@ int ecpic2d_create(const ecpic2d_config *cfg, ecpic2d_ctx **out) {
     const int M1 = c->M1, M2 = c->M2;
     fill_dir(M1, dx1, &sy[0], &sy[M1], &sy[2 * M1], &sy[3 * M1]);
     fill_dir(M2, dx2, &sy[4 * M1], &sy[4 * M1 + M2], &sy[4 * M1 + 2 * M2], &sy[4 * M1 + 3 * M2]);
-    bool ok = hipMemcpy(c->tw1, t1.data(), sizeof(double2) * t1.size(), hipMemcpyHostToDevice) == hipSuccess &&
+    // First rows of the inverses of the 1D mass matrices, from their eigenvalues lam:
+    // c_m = (1/M) sum_k cos(2 pi k m / M) / lam_k, kept while above 1e-18 c_0 (the whole
+    // period if it is shorter).
+    auto inverse_row = [&](int M, const double *lam, std::vector<double> &row, int &hi) {
+        std::vector<long double> cs(M), inv(M);
+        for (int k = 0; k < M; ++k) {
+            cs[k] = cosl(2 * PI * k / M);
+            inv[k] = 1.0L / (long double)lam[k];
+        }
+        auto entry = [&](int m) {
+            long double v = 0;
+            for (int k = 0; k < M; ++k) v += inv[k] * cs[(int)(((int64_t)k * m) & (M - 1))];
+            return (double)(v / M);
+        };
+        std::vector<double> half(1, entry(0));
+        while ((int)half.size() < M / 2 && std::fabs(half.back()) > 1e-18 * half[0]) half.push_back(entry((int)half.size()));
+        const bool whole = (int)half.size() >= M / 2;
+        const int lo = whole ? M / 2 - 1 : (int)half.size() - 1;   // offsets -lo .. hi
+        hi = whole ? M / 2 : lo;
+        if (whole) half.resize(M / 2), half.push_back(entry(M / 2));
+        row.assign(lo + hi + 1, 0.0);
+        for (int m = -lo; m <= hi; ++m) row[hi - m] = half[std::abs(m)];   // reversed: first the largest offset
+    };
+    auto conv_taps = [&](int M, const double *m0, const double *m1, bool first_is_m1, ConvTaps &t) {
+        for (int b = 0; b < 2; ++b) {
+            std::vector<double> row;
+            inverse_row(M, (b == 0) == first_is_m1 ? m1 : m0, row, t.hi[b]);
+            t.nt[b] = (int)row.size();
+            std::vector<double> pad(8 + conv_steps(t.nt[b]) + 16, 0.0);
+            std::copy(row.begin(), row.end(), pad.begin() + 8);
+            double *d = nullptr;
+            if (dalloc(c, &d, pad.size()) ||
+                hipMemcpy(d, pad.data(), sizeof(double) * pad.size(), hipMemcpyHostToDevice) != hipSuccess)
+                return false;
+            t.rt[b] = d + 8;
+        }
+        return true;
+    };
+    // component 1: m1(x1) m0(x2), component 2: m0(x1) m1(x2)
+    bool ok = conv_taps(M1, &sy[0], &sy[M1], true, c->conv_a) &&
+              conv_taps(M2, &sy[4 * M1], &sy[4 * M1 + M2], false, c->conv_b);
+    ok = ok && hipMemcpy(c->tw1, t1.data(), sizeof(double2) * t1.size(), hipMemcpyHostToDevice) == hipSuccess &&
               hipMemcpy(c->tw2, t2.data(), sizeof(double2) * t2.size(), hipMemcpyHostToDevice) == hipSuccess &&
               hipMemcpy(c->sym, sy.data(), sizeof(double) * sy.size(), hipMemcpyHostToDevice) == hipSuccess;
     if (!ok) { ecpic2d_destroy(c); return ECPIC_EDEVICE; }
     for (double **gp : grids) k2_fill<<<grid_for(c->Nc), BLOCK, 0, c->stream>>>(*gp, c->Nc, 0.0);
     k2_fill_i32<<<grid_for(c->Nc), BLOCK, 0, c->stream>>>(c->count, c->Nc);
     // the commit accumulates arrivals per tile: every tile counter starts at zero
-    for (int32_t *tp : {c->tstay, c->tarr, c->tcnt})
+    for (int32_t *tp : {c->tstay, c->tarr})
         k2_fill_i32<<<grid_for(c->ntiles), BLOCK, 0, c->stream>>>(tp, c->ntiles);
     k2_fill_i32<<<1, 1, 0, c->stream>>>(c->flags, 1);
+    k2_fill_i32<<<1, 2, 0, c->stream>>>(c->gate, 2);   // gate[1] stays open
+    k2_fill_i32<<<1, 1, 0, c->stream>>>(reinterpret_cast<int32_t *>(c->done), 1);
     if (sync2(c)) { ecpic2d_destroy(c); return ECPIC_EDEVICE; }
     *out = c;
     return ECPIC_OK;
@@ -2537,8 +2978,6 @@ int ecpic2d_destroy(ecpic2d_ctx *c) {
     for (auto &pe : c->prof.pending) { hipEventDestroy(pe.second.first); hipEventDestroy(pe.second.second); }
     for (void *p : c->allocs) hipFree(p);
     if (c->hres) hipHostFree(c->hres);
-    for (hipEvent_t e : c->ev)
-        if (e) hipEventDestroy(e);
     if (c->stream) hipStreamDestroy(c->stream);
     delete c;
     return ECPIC_OK;
@@ -2565,7 +3004,7 @@ int ecpic2d_set_particles(ecpic2d_ctx *c, const double *x1, const double *x2, co
     (void)B;
     k2_fill_i32<<<1, 1, 0, s>>>(c->flags, 1);
     k2_fill_i32<<<grid_for(c->Nc), BLOCK, 0, s>>>(c->count, c->Nc);
-    for (int32_t *tp : {c->tstay, c->tarr, c->tcnt})
+    for (int32_t *tp : {c->tstay, c->tarr})
         k2_fill_i32<<<grid_for(c->ntiles), BLOCK, 0, s>>>(tp, c->ntiles);
     k2_iota<<<grid_for(n), BLOCK, 0, s>>>(c->id[A], n);
     k2_bin_new<<<grid_for(n), BLOCK, 0, s>>>(c->d1[0], c->d2[0], c->xi1[A], c->xi2[A], c->cell, c->count, n,
@@ -2682,7 +3121,8 @@ int ecpic2d_substep_I(ecpic2d_ctx *c, double dt, ecpic2d_iter_stats *st) {
     if (!c || !(dt > 0) || !(dt < std::min(c->dx1, c->dx2))) return ECPIC_EINVAL;
     if (!c->have_particles) return ECPIC_ESTATE;
     hipSetDevice(c->device);
-    return substep_I(c, dt, st);
+    const int rc = substep_I(c, dt, st);
+    return rc ? rc : sync2(c);
 }
 
 int ecpic2d_substep_II(ecpic2d_ctx *c, double dt) {
