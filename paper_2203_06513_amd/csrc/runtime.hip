@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "../../include/ecpic.h"
+#include "hostcopy.hpp"
 #include "internal.hpp"
 
 namespace ecpic {
@@ -287,6 +288,7 @@ struct ecpic_ctx {
     double *spart = nullptr;        // [max_items][2 deg] spin deposit per item (Subsystem II source)
     double *epart = nullptr;        // [max_items] Zeeman sum per item
     std::vector<double> h_epart;
+    HostCopy host_copy;             // large arrays to the caller's memory
     Prof prof;
 };
 
@@ -815,6 +817,7 @@ void free_all(ecpic_ctx *c) {
     F(c->ws_pgrad); F(c->ws_ploss); F(c->ws_loss); F(c->ws_w2b);
     F(c->rho); F(c->rvec); F(c->uvec); F(c->out5); F(c->part_e); F(c->maxbits); F(c->count); F(c->ex_save);
     if (c->h_ring) hipHostFree(c->h_ring);
+    c->host_copy.release();
     for (auto &e : c->prof.pool) hipEventDestroy(e);
     for (auto &pe : c->prof.pending) { hipEventDestroy(pe.second.first); hipEventDestroy(pe.second.second); }
     if (c->own_stream && c->stream) hipStreamDestroy(c->stream);
@@ -1110,8 +1113,9 @@ int ecpic_get_particles(ecpic_ctx *c, double *x, double *p, int64_t n) {
     if (dalloc(&dx_, n) || dalloc(&dp_, n)) { if (dx_) hipFree(dx_); return ECPIC_ENOMEM; }
     int rc = ecpic_get_particles_dev(c, dx_, dp_, n);
     if (rc == ECPIC_OK && n > 0) {
-        if (hipMemcpy(x, dx_, sizeof(double) * n, hipMemcpyDeviceToHost) != hipSuccess ||
-            hipMemcpy(p, dp_, sizeof(double) * n, hipMemcpyDeviceToHost) != hipSuccess)
+        const size_t bytes = sizeof(double) * (size_t)n;
+        if (c->host_copy.to_host(x, dx_, bytes, c->stream, c->device) != hipSuccess ||
+            c->host_copy.to_host(p, dp_, bytes, c->stream, c->device) != hipSuccess)
             rc = ECPIC_EDEVICE;
     }
     hipFree(dx_);
@@ -1156,7 +1160,7 @@ int ecpic_get_spins(ecpic_ctx *c, double *sx, double *sy, double *sz, int64_t n)
     int rc = ECPIC_OK;
     double *out[3] = {sx, sy, sz};
     for (int k = 0; k < 3 && rc == ECPIC_OK; ++k)
-        if (hipMemcpyAsync(out[k], t[k], sizeof(double) * n, hipMemcpyDeviceToHost, c->stream) != hipSuccess)
+        if (c->host_copy.to_host(out[k], t[k], sizeof(double) * (size_t)n, c->stream, c->device) != hipSuccess)
             rc = ECPIC_EDEVICE;
     if (rc == ECPIC_OK) rc = sync(c);
     for (double *q : t) hipFree(q);

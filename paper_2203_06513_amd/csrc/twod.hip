@@ -44,6 +44,7 @@
 #include "../../include/ecpic2d.h"
 #include "coef.hpp"
 #include "common.hpp"
+#include "hostcopy.hpp"
 #include "spline.hpp"
 
 namespace ecpic2d {
@@ -2409,6 +2410,7 @@ struct ecpic2d_ctx {
     int keep_from = 0, last_k = 0;       // first sweep that stores its momentum; last sweep of the last substep
     bool have_particles = false;
     std::vector<double> m0row, m1row;
+    ecpic::HostCopy host_copy;   // large arrays to the caller's memory
     Prof2 prof;
     std::vector<void *> allocs;
 };
@@ -2976,6 +2978,7 @@ int ecpic2d_destroy(ecpic2d_ctx *c) {
     hipSetDevice(c->device);
     if (c->stream) hipStreamSynchronize(c->stream);
     for (auto &pe : c->prof.pending) { hipEventDestroy(pe.second.first); hipEventDestroy(pe.second.second); }
+    c->host_copy.release();
     for (void *p : c->allocs) hipFree(p);
     if (c->hres) hipHostFree(c->hres);
     if (c->stream) hipStreamDestroy(c->stream);
@@ -3048,10 +3051,7 @@ int ecpic2d_get_spins(ecpic2d_ctx *c, double *sx, double *sy, double *sz, int64_
     const double *srcs[3] = {c->sx[A], c->sy[A], c->sz[A]};
     for (int q = 0; q < 3 && n > 0; ++q) {
         k2_unsort<<<grid_for(n), BLOCK, 0, c->stream>>>(srcs[q], c->id[A], c->pk1, n, 1.0);
-        if (hipMemcpyAsync(outs[q], c->pk1, bytes, hipMemcpyDeviceToHost, c->stream) != hipSuccess)
-            return ECPIC_EDEVICE;
-        int rc = sync2(c);
-        if (rc) return rc;
+        if (c->host_copy.to_host(outs[q], c->pk1, bytes, c->stream, c->device) != hipSuccess) return ECPIC_EDEVICE;
     }
     return sync2(c);
 }
@@ -3068,10 +3068,7 @@ int ecpic2d_get_particles(ecpic2d_ctx *c, double *x1, double *x2, double *p1, do
     for (int q = 0; q < 4; ++q) {
         if (n == 0) break;
         k2_unsort<<<grid_for(n), BLOCK, 0, c->stream>>>(srcs[q], c->id[A], c->pk1, n, scales[q]);
-        if (hipMemcpyAsync(outs[q], c->pk1, bytes, hipMemcpyDeviceToHost, c->stream) != hipSuccess)
-            return ECPIC_EDEVICE;
-        int rc = sync2(c);
-        if (rc) return rc;
+        if (c->host_copy.to_host(outs[q], c->pk1, bytes, c->stream, c->device) != hipSuccess) return ECPIC_EDEVICE;
     }
     return sync2(c);
 }
