@@ -74,6 +74,8 @@ struct Particles {
     double *sx, *sy, *sz;   // spins (null without spin); Subsystem I carries them with the sort
 };
 
+constexpr int UNPERMUTE_BUCKETS = 1024;   // most buckets of a particle readout in two passes
+
 // ---- learned warm start ----------------------------------------------------
 // A multilayer perceptron D -> 64 -> 64 -> 2 (GELU, tanh form) predicts the
 // converged increment of Subsystem I from a particle's local state.  It is

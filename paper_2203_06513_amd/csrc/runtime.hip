@@ -74,7 +74,7 @@ void launch_count_cells_xi(hipStream_t s, const double *xi, int64_t n, int M, in
 void launch_items_from_counts(hipStream_t s, const int32_t *count, int32_t *start, int M, int chunk, int64_t N,
                               ItemList out);
 void launch_unpermute(hipStream_t s, const double *xi, const double *p, const int32_t *id, int64_t n, double dx,
-                      double *x_out, double *p_out);
+                      double *x_out, double *p_out, Particles tmp, int32_t *cursor);
 void launch_deposit_segments(int P, hipStream_t s, const double *x0, const double *x1, int64_t n, double inv_dx,
                              double dx, double w, int M, double *J, int *flags);
 void launch_copy(hipStream_t s, const double *in, double *out, int64_t n);
@@ -268,6 +268,7 @@ struct ecpic_ctx {
     bool symmetric = false;      // steps are I(dt/2), II(dt), adjoint I(dt/2)
     unsigned long long *maxbits = nullptr;
     int32_t *count = nullptr;
+    int32_t *cursor = nullptr;   // bucket cursors of a large readout
     bool have_particles = false;
     // previous-step warm start: the increment each commit took, in the new order
     bool ws_prev = false;
@@ -815,7 +816,7 @@ void free_all(ecpic_ctx *c) {
     F(c->st_ring);
     F(c->ws_theta); F(c->ws_m); F(c->ws_v); F(c->ws_norm); F(c->ws_table); F(c->ws_feat); F(c->ws_targ);
     F(c->ws_pgrad); F(c->ws_ploss); F(c->ws_loss); F(c->ws_w2b);
-    F(c->rho); F(c->rvec); F(c->uvec); F(c->out5); F(c->part_e); F(c->maxbits); F(c->count); F(c->ex_save);
+    F(c->rho); F(c->rvec); F(c->uvec); F(c->out5); F(c->part_e); F(c->maxbits); F(c->count); F(c->cursor); F(c->ex_save);
     if (c->h_ring) hipHostFree(c->h_ring);
     c->host_copy.release();
     for (auto &e : c->prof.pool) hipEventDestroy(e);
@@ -887,6 +888,7 @@ int alloc_all(ecpic_ctx *c) {
     rc |= dalloc(&c->rho, M); rc |= dalloc(&c->rvec, M); rc |= dalloc(&c->uvec, M);
     rc |= dalloc(&c->out5, 8); rc |= dalloc(&c->part_e, c->max_items); rc |= dalloc(&c->maxbits, 1);
     rc |= dalloc(&c->count, M);
+    rc |= dalloc(&c->cursor, UNPERMUTE_BUCKETS);
     if (c->symmetric || c->spin) rc |= dalloc(&c->ex_save, MP);
     if (c->spin) {
         rc |= dalloc(&c->spart, (size_t)c->max_items * 2 * c->P);
@@ -1101,7 +1103,8 @@ int ecpic_get_particles_dev(ecpic_ctx *c, double *x, double *p, int64_t n) {
     if (!c->have_particles) return ECPIC_ESTATE;
     hipSetDevice(c->device);
     const Particles &d = c->pb[c->cur];
-    launch_unpermute(c->stream, d.xi, d.p, d.id, n, c->dx, x, p);
+    // the other particle buffer holds nothing between calls: scratch of a large readout
+    launch_unpermute(c->stream, d.xi, d.p, d.id, n, c->dx, x, p, c->pb[c->cur ^ 1], c->cursor);
     return sync(c);
 }
 

@@ -1,7 +1,8 @@
-"""Large readouts go through a pinned ring: 2 MiB slots, 16 of them, from 8 MiB up.
+"""Large readouts go to the host through a pinned ring: 2 MiB slots, 16 of them, from 8 MiB
+up.  On the device the particles return to their order in two passes past 2^24 of them.
 
 Tolerance: momenta and spins are stored and returned as given, so they are equal bit by
-bit; positions pass through cell units (one product each way), hence a few ulp of L.
+bit; steps are deterministic; positions pass through cell units (one product each way), hence a few ulp of L.
 """
 import numpy as np
 import pytest
@@ -35,6 +36,33 @@ def test_1d_round_trip(n):
         for a, b in zip(ctx.get_spins(), s):
             assert np.array_equal(a, b)
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [1 << 24,                     # one pass
+                               (1 << 24) + 1,               # two passes, a last tile of one particle
+                               (1 << 24) + 5 * 16384 - 1,   # a last tile one short
+                               20_000_003])
+def test_1d_device_readout_in_two_passes(n):
+    """The readout leaves the state alone: steps after it are those without it."""
+    torch = pytest.importorskip("torch")
+    g = torch.Generator(device="cuda").manual_seed(n)
+    L = 32.0
+    x = torch.rand(n, dtype=torch.float64, device="cuda", generator=g) * (0.999 * L)
+    p = torch.randn(n, dtype=torch.float64, device="cuda", generator=g) * 0.05
+    out = []
+    for read in (True, False):
+        ctx = ec.Context(L=L, M=256, degree=2, n_particles=n, dt=0.01, tol=1e-10)
+        ctx.set_particles_dev(x.data_ptr(), p.data_ptr())
+        gx, gp = torch.full_like(x, -1.0), torch.full_like(p, float("nan"))
+        if read:
+            ctx.get_particles_dev(gx.data_ptr(), gp.data_ptr())
+            assert torch.equal(gp, p)
+            assert float((gx - x).abs().max()) <= 4 * np.finfo(float).eps * L
+        ctx.step(1)
+        ctx.get_particles_dev(gx.data_ptr(), gp.data_ptr())
+        out.append((gx, gp))
+        ctx.close()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
 
 
 @pytest.mark.parametrize("n", SIZES)
