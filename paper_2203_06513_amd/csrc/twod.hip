@@ -2470,15 +2470,17 @@ Sym sym_of(ecpic2d_ctx *c) {
 
 int n_tiles(ecpic2d_ctx *c) { return c->M1 * (c->M2 / c->TW); }
 
-// Blocks per tile of the particle passes: enough that the launch has about 1024
-// blocks (the chip holds 512 to 1536 of them), as long as every wave keeps a row of
-// 64 particles on average.  Each block stages its own patch and adds its own deposits
-// to the grid, so more blocks than that cost: 128 tiles (128 x 64 cells, 5e5 quintic
-// particles) sweep 112 -> 79 us, III deposit 45 -> 27 us with 8 blocks each; 1024
-// tiles (256 x 256, 2^22 with spin) sweep 180 us with one block, 194 with two.
+// Blocks per tile of the particle passes: enough that the launch has 512 blocks, the
+// number that the sweeps of high degree or with spin keep resident (two a CU), as long
+// as every wave keeps a row of 64 particles on average.  Each block stages its own
+// patch, finishes its own crossing particles and adds its own deposits to the grid, so a
+// second round of blocks costs: 128 tiles (128 x 64 cells, 5e5 quintic particles) sweep
+// 71 us with 2 blocks a tile, 66 with 4, 81 with 8; 256 tiles (64 x 256, 3.6e5 quintic
+// with spin) 75 us with 1, 67 with 2, 101 with 4, cubic without spin 25.2, 24.9 and 36;
+// 1024 tiles (256 x 256, 2^22 with spin) 180 us with one block, 194 with two.
 int blocks_per_tile(ecpic2d_ctx *c) {
     const int64_t nt = n_tiles(c), rows = c->N / nt / BLOCK;   // rows of a tile per wave of one block
-    return (int)std::max<int64_t>(1, std::min<int64_t>(1024 / nt, rows));
+    return (int)std::max<int64_t>(1, std::min<int64_t>(512 / nt, rows));
 }
 
 // Full cell sort (set_particles): counts in c->count, cells in c->cell; each tile
