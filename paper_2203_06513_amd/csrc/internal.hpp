@@ -190,6 +190,10 @@ struct SpinArgs {
     double h;                // rotation time (Subsystem III)
     double *spart;           // [items][2 deg] V1 sums of (s_y, s_z) per item (deposit pass)
     double *epart;           // [items] Zeeman sum per item (energy pass)
+    // a pass queued ahead runs only if this substep was let run (its gate) or, with
+    // gate_committed, if it committed; null: always
+    const DevStatus *gate;
+    int32_t gate_committed;
 };
 
 // ---- Subsystem II --------------------------------------------------------

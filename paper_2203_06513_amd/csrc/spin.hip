@@ -64,13 +64,18 @@ __device__ __forceinline__ void dadx(const CellDiff<P> &d, double t, double &Y, 
 
 __device__ __forceinline__ double local_t(double xi, int c) { return fmin(fmax(xi - (double)c, 0.0), 1.0); }
 
+// Whether a pass queued behind a substep may run (see SpinArgs::gate).
+__device__ __forceinline__ bool gate_open(const DevStatus *st, int committed) {
+    return !st || (committed ? st->committed && st->flags == 0 : st->gate);
+}
+
 // Subsystem III over h: s <- exp(h rhat) s, rhat s = r x s, r = (0, Z, -Y), by
 // Rodrigues' formula s + c1 (r x s) + c2 r x (r x s) with c1 = sin(h|r|)/|r| and
 // c2 = 2 sin^2(h|r|/2)/|r|^2 (the limits h and h^2/2 at r = 0).
 template <int P>
 __global__ void __launch_bounds__(256) k_spin_rotate(SpinArgs a, int M) {
     CellDiff<P> d;
-    if (!cell_diff<P>(a, blockIdx.x, M, d)) return;
+    if (!gate_open(a.gate, a.gate_committed) || !cell_diff<P>(a, blockIdx.x, M, d)) return;
 #pragma unroll 2
     for (int i = d.beg + (int)threadIdx.x; i < d.end; i += blockDim.x) {
         const double t = local_t(a.xi[i], d.c);
@@ -102,7 +107,7 @@ template <int P>
 __global__ void __launch_bounds__(256) k_spin_deposit(SpinArgs a, int M) {
     __shared__ double lds[MAX_WAVES][2 * P];
     CellDiff<P> d;
-    if (!cell_diff<P>(a, blockIdx.x, M, d)) return;
+    if (!gate_open(a.gate, a.gate_committed) || !cell_diff<P>(a, blockIdx.x, M, d)) return;
     double vy[P], vz[P];
 #pragma unroll
     for (int m = 0; m < P; ++m) { vy[m] = 0.0; vz[m] = 0.0; }
@@ -140,7 +145,8 @@ __global__ void __launch_bounds__(256) k_spin_deposit(SpinArgs a, int M) {
 template <int P>
 __global__ void __launch_bounds__(256) k_spin_source(const double *spart, ItemList items, int M, double coef,
                                                      const double *taps, int ntaps, int mlo, double *E0y,
-                                                     double *E0z) {
+                                                     double *E0z, const DevStatus *gate) {
+    if (!gate_open(gate, 0)) return;
     extern __shared__ double sh[];
     const int len = blockDim.x + ntaps - 1;            // b indices lo .. lo + len - 1
     const int j0 = blockIdx.x * blockDim.x;
@@ -243,10 +249,10 @@ void launch_spin_deposit(int P, int grid, hipStream_t s, const SpinArgs &a, int 
 }
 
 void launch_spin_source(int P, hipStream_t s, const double *spart, const ItemList &items, int M, double coef,
-                        const double *taps, int ntaps, int mlo, double *E0y, double *E0z) {
+                        const double *taps, int ntaps, int mlo, double *E0y, double *E0z, const DevStatus *gate) {
     const size_t lds = sizeof(double) * (4 * (size_t)(256 + ntaps - 1) + 2);
     ECPIC_SPIN_P(k_spin_source, dim3((M + 255) / 256), dim3(256), lds, s, spart, items, M, coef, taps, ntaps, mlo,
-                 E0y, E0z)
+                 E0y, E0z, gate)
 }
 
 void launch_spin_energy(int P, int grid, hipStream_t s, const SpinArgs &a, int M) {

@@ -334,6 +334,14 @@ __global__ void __launch_bounds__(256) k_field_II(FieldIIArgs a) {
     }
 }
 
+// The words of a status before the residual history, written straight into the host's
+// pinned copy by the first threads of a block.
+constexpr int MIRROR_WORDS = (int)(offsetof(DevStatus, res_hist) / sizeof(int32_t));
+__device__ __forceinline__ void mirror_status(DevStatus *mirror, const DevStatus *st, int t) {
+    if (t >= 0 && t < MIRROR_WORDS)
+        reinterpret_cast<int32_t *>(mirror)[t] = reinterpret_cast<const int32_t *>(st)[t];
+}
+
 struct Stencil {
     double v[2 * MAX_DEG + 1];
     int half;
@@ -441,8 +449,9 @@ __host__ __device__ constexpr size_t step_start_lds(int P, int ntaps) {
 // Start of a step (or of one substep).  Block 0 resets the statuses it is
 // given (stI for Subsystem I, gated on gate_src, the Subsystem II status of the
 // step before when it was enqueued ahead; stII for a Subsystem II run on its
-// own; in a full step the Subsystem I commit resets stII).  A gated-off step
-// writes nothing else.  Block b, on cells
+// own; in a full step the Subsystem I commit resets stII) and, with mirror, writes
+// gate_src to the host's copy of it.  A gated-off step writes nothing else.  With keep,
+// that padded field (e_x at the start of a symmetric step) is saved in keep_to.  Block b, on cells
 // b * FIELD2_OUT .. + FIELD2_OUT - 1, writes the A-records of a^n (shared by
 // both substeps, Subsystem I leaves a_perp alone), with do_I the E-records of
 // e_x^n, and with do_II the A-records of a^(0) = a^n - dt e^n (the iterate for
@@ -454,7 +463,8 @@ template <int P>
 __global__ void __launch_bounds__(256) k_begin_step(DevStatus *stI, const DevStatus *gate_src, DevStatus *stII,
                                                     const double *ayn, const double *azn, const double *eyn,
                                                     const double *ezn, const double *exn, const double *taps,
-                                                    StepStart a) {
+                                                    StepStart a, DevStatus *mirror, const double *keep,
+                                                    double *keep_to) {
     extern __shared__ double R[];
     // a step enqueued behind another runs only if that one committed
     const bool go = gate_src ? (gate_src->committed && gate_src->flags == 0) : true;
@@ -462,6 +472,7 @@ __global__ void __launch_bounds__(256) k_begin_step(DevStatus *stI, const DevSta
         if (stI) init_status(stI, gate_src);
         if (stII) init_status(stII, nullptr);
     }
+    if (mirror && blockIdx.x == 0) mirror_status(mirror, gate_src, threadIdx.x);
     const int M = a.M, ntaps = a.ntaps;
     const int j0 = blockIdx.x * FIELD2_OUT;
     const int mhi = a.mlo + ntaps - 1;
@@ -480,6 +491,8 @@ __global__ void __launch_bounds__(256) k_begin_step(DevStatus *stI, const DevSta
     const double w_ex = exn ? exn[imod(j0 - P + min(t, XL - 1), M) + HALO] : 0.0;
     asm volatile("" ::"v"(w_ay), "v"(w_az), "v"(w_ey), "v"(w_ez), "v"(w_tp), "v"(w_ex));
     if (!go) return;
+    if (keep)
+        for (int i = blockIdx.x * blockDim.x + t; i < M + 2 * HALO; i += gridDim.x * blockDim.x) keep_to[i] = keep[i];
     if (t < wlen) { Way[t] = w_ay; Waz[t] = w_az; Wey[t] = w_ey; Wez[t] = w_ez; }
     for (int idx = t + blockDim.x; idx < wlen; idx += blockDim.x) {
         const int j = imod(wlo + idx, M) + HALO;
@@ -547,12 +560,8 @@ __global__ void __launch_bounds__(256) k_step_join(JoinArgs g, StepStart a) {
         if (t == 0 && kc >= 0) st->committed = 1;
         if (g.mirror) {   // the words before the residual history of both statuses
             __syncthreads();
-            constexpr int W = (int)(offsetof(DevStatus, res_hist) / sizeof(int32_t));
-            if (t < 2 * W) {
-                const int32_t *src = reinterpret_cast<const int32_t *>(t < W ? g.stI : st);
-                int32_t *dst = reinterpret_cast<int32_t *>(g.mirror + (t < W ? 0 : 1));
-                dst[t % W] = src[t % W];
-            }
+            mirror_status(g.mirror, g.stI, t);
+            mirror_status(g.mirror + 1, st, t - MIRROR_WORDS);
         }
         if (t == 0) init_status(g.stI_next, st);
     }
@@ -630,16 +639,9 @@ __global__ void __launch_bounds__(256) k_commit_II(DevStatus *st, const DevStatu
         }
     }
     if (mirror && blockIdx.x == 0) {
-        // the host's copy of both statuses (the words before the residual
-        // history), written straight into its pinned mirror
-        __syncthreads();
-        constexpr int W = (int)(offsetof(DevStatus, res_hist) / sizeof(int32_t));
-        const int t = threadIdx.x;
-        if (t < 2 * W) {
-            const int32_t *src = reinterpret_cast<const int32_t *>(t < W ? stI : st);
-            int32_t *dst = reinterpret_cast<int32_t *>(mirror + (t < W ? 0 : 1));
-            dst[t % W] = src[t % W];
-        }
+        __syncthreads();   // thread 0 has recorded the commit
+        mirror_status(mirror, stI, threadIdx.x);
+        mirror_status(mirror + 1, st, (int)threadIdx.x - MIRROR_WORDS);
     }
 }
 
@@ -668,7 +670,8 @@ void launch_begin_step(int P, hipStream_t s, DevStatus *stI, const DevStatus *ga
                        const double *ayn, const double *azn,
                        const double *eyn, const double *ezn, const double *exn, double dt, double *coefA,
                        double *coefE0, double *coefAk0, int do_II, const double *m0, const double *kr, double r2,
-                       double ck, const double *taps, int ntaps, int mlo, int M, double *E0y, double *E0z) {
+                       double ck, const double *taps, int ntaps, int mlo, int M, double *E0y, double *E0z,
+                       DevStatus *mirror, const double *keep, double *keep_to) {
     StepStart a{};
     a.coefA = coefA; a.coefE0 = coefE0; a.coefAk0 = coefAk0; a.E0y = E0y; a.E0z = E0z;
     a.m0.half = P; a.kk.half = P;
@@ -679,7 +682,7 @@ void launch_begin_step(int P, hipStream_t s, DevStatus *stI, const DevStatus *ga
 #define ECPIC_B2(PP)                                                                                          \
     case PP:                                                                                                  \
         launch_k((k_begin_step<PP>), dim3(grid), dim3(256), lds, s, stI, gate_src, stII, ayn, azn, eyn, ezn, \
-                 exn, taps, a);                                                                               \
+                 exn, taps, a, mirror, keep, keep_to);                                                        \
         break;
     switch (P) { ECPIC_B2(2) ECPIC_B2(3) ECPIC_B2(4) ECPIC_B2(5) }
 #undef ECPIC_B2
