@@ -101,6 +101,18 @@ struct WsRecord {
 };
 
 // ---- Subsystem I ---------------------------------------------------------
+// On a small grid the field update has no kernel of its own: the next sweep, or the
+// commit, opens with it, every block forming the whole field (see small_field_I).
+constexpr int SMALL_CELLS = 128, SMALL_THREADS = 256;
+struct SmallI {
+    const double *part[2];         // wave partials and mover counts of a sweep, by its parity
+    const int32_t *wcnt[2];
+    const double *taps, *en;       // as in FieldIArgs
+    double *ek0, *ek1;
+    double w;
+    int32_t ntaps, mlo, M, wpi;
+};
+
 struct SweepIArgs {
     const double *xi, *p;
     double *d0, *d1;               // iterate buffers, d^(k) = k&1 ? d1 : d0
@@ -125,6 +137,7 @@ struct SweepIArgs {
     // spin force (sweeps compiled with it): s_y, s_z and hbar / dx^2
     const double *sy, *sz;
     double hbar_dx2;
+    SmallI small;                  // sweeps compiled to open with the field update
 };
 
 struct FieldIArgs {
@@ -178,6 +191,8 @@ struct CommitIArgs {
     WsRecord rec;                  // training pairs to record (rec.stride 0: none)
     double *dprev_out;             // non-null: the committed increment, in the new order
     int64_t N;
+    SmallI small;                  // commits compiled to open with the field update ...
+    double *ex_next;               // ... which also form e_x^{n+1} (padded)
 };
 
 // ---- spin (Subsystem III, the Subsystem II source, the Zeeman energy) -------
@@ -197,6 +212,18 @@ struct SpinArgs {
 };
 
 // ---- Subsystem II --------------------------------------------------------
+// The same for Subsystem II: the field update of an iterate opens the next particle pass,
+// the commit or the join.
+struct SmallII {
+    ItemList items, items0;        // items of the passes, and of iterate 0's partials
+    const double *part[2];         // wave partials of an iterate, by its parity
+    const double *taps, *E0y, *E0z, *eyn, *ezn, *ayn, *azn;   // as in FieldIIArgs
+    double *ey0, *ey1, *ez0, *ez1;
+    double coef, half_dt;
+    int32_t ntaps, mlo, M, wpi;
+    int32_t wide0;                 // iterate 0's partials come from the commit, 2 (deg+3) per wave
+};
+
 struct SweepIIArgs {
     const double *xi, *p;
     ItemList items;
@@ -206,6 +233,7 @@ struct SweepIIArgs {
     DevStatus *st;
     double tol;
     int32_t k;
+    SmallII small;                            // passes compiled to open with the field update
 };
 
 struct FieldIIArgs {

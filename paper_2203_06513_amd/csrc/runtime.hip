@@ -44,13 +44,14 @@ void launch_step_join(int P, hipStream_t s, DevStatus *st, const DevStatus *stI,
                       double *ez_next, double *ay_next, double *az_next, int nsweeps, double tol,
                       const double *exn_next, double dt, double *coefA, double *coefE0, double *coefAk0,
                       const double *m0, const double *kr, double r2, double ck, const double *taps, int ntaps,
-                      int mlo, int M, double *E0y, double *E0z);
+                      int mlo, int M, double *E0y, double *E0z, const SmallII &small);
 void launch_conv(int grid, hipStream_t s, const double *in, double *out, const double *taps, int ntaps, int mlo,
                  double alpha, int M);
-void launch_commit_II(int grid, hipStream_t s, DevStatus *st, const DevStatus *stI, DevStatus *mirror,
+void launch_commit_II(int P, int grid, hipStream_t s, DevStatus *st, const DevStatus *stI, DevStatus *mirror,
                       const double *eyn, const double *ezn, const double *ayn, const double *azn, const double *ey0,
                       const double *ey1, const double *ez0, const double *ez1, double *ey_next, double *ez_next,
-                      double *ay_next, double *az_next, double half_dt, int M, int nsweeps, double tol);
+                      double *ay_next, double *az_next, double half_dt, int M, int nsweeps, double tol,
+                      const SmallII &small);
 void launch_energy(int P, int grid, int block, hipStream_t s, const double *xi, const double *p, ItemList items,
                    const double *ay, const double *az, double *part);
 void launch_energy_final(hipStream_t s, const double *part, const int32_t *n_items, double w, const double *ex,
@@ -268,6 +269,8 @@ struct ecpic_ctx {
     double *ex_save = nullptr;   // e_x at the start of a symmetric step (its rollback)
     bool symmetric = false;      // steps are I(dt/2), II(dt), adjoint I(dt/2)
     unsigned long long *maxbits = nullptr;
+    SmallII smallII{};        // the field update of the Subsystem II iterates last queued, on a small grid
+    size_t part_stride = 0;   // distance of the buffers of wave partials on a small grid (0: one buffer)
     int32_t *count = nullptr;
     int32_t *cursor = nullptr;   // bucket cursors of a large readout
     bool have_particles = false;
@@ -388,6 +391,33 @@ SweepIArgs sweep_args(ecpic_ctx *c) {
     return a;
 }
 
+// The field updates of Subsystem I open the sweeps and commits (small grids; the plain
+// FP64 sweeps, no training pairs to record).
+bool small_grid(const ecpic_ctx *c) { return c->part_stride > 0 && !c->k32 && !c->ws_on && !c->ws_stride; }
+
+SmallI small_args(const ecpic_ctx *c) {
+    SmallI f{};
+    if (!small_grid(c)) return f;
+    const int wpi = c->block / 64;
+    for (int b = 0; b < 2; ++b) {
+        f.part[b] = c->part + b * c->part_stride;
+        f.wcnt[b] = c->wcnt + (size_t)b * c->max_items * wpi * 3;
+    }
+    f.taps = c->taps1;
+    f.ntaps = c->nt1;
+    f.mlo = c->mlo1;
+    f.en = c->ex[c->exc];
+    f.ek0 = c->ek[0];
+    f.ek1 = c->ek[1];
+    f.w = c->w;
+    f.M = c->M;
+    f.wpi = wpi;
+    return f;
+}
+
+// Subsystem II's wave partials (of iterate k on a small grid): behind those of Subsystem I where a commit still reads them.
+double *part_II(const ecpic_ctx *c, int k = 0) { return c->part + (k & 1 ? 0 : 2) * c->part_stride; }
+
 // Index of the first FP64 sweep of a Subsystem I substep: after the predictor
 // pass (learned warm start) and the FP32 sweeps (precision form); the adjoint
 // substep has neither.
@@ -426,8 +456,14 @@ void enqueue_sweeps_I(ecpic_ctx *c, int count) {
     a.explicit_start = !mlp && !a.dprev;
     a.ws = WsNet{c->ws_theta, c->ws_norm, c->ws_norm + (c->wsD + 2), c->ws_norm + 2 * (c->wsD + 2)};
     a.ws_table = c->ws_table;
+    a.small = small_args(c);
+    const bool small = a.small.M > 0;
     for (int i = 0; i < count; ++i) {
         a.k = f.k = c->kI++;
+        if (small) {
+            a.part = c->part + (a.k & 1) * c->part_stride;
+            a.wcnt = c->wcnt + (size_t)(a.k & 1) * c->max_items * f.wpi * 3;
+        }
         if (mlp && a.k == 0) {   // the predictor pass takes the place of sweep 0
             timed(c, "ws_predict", [&] { launch_ws_predict(c->P, gridp, c->block, c->stream, a); });
         } else {
@@ -437,7 +473,7 @@ void enqueue_sweeps_I(ecpic_ctx *c, int count) {
                 launch_sweep_I(c->P, c->seidel || c->adjoint, fp32, c->adjoint, gridp, c->block, c->stream, a);
             });
         }
-        timed(c, "field_I", [&] { launch_field_I(c->P, c->M, c->stream, f); });
+        if (!small) timed(c, "field_I", [&] { launch_field_I(c->P, c->M, c->stream, f); });
     }
 }
 
@@ -492,8 +528,10 @@ void enqueue_commit_I(ecpic_ctx *c) {
     a.list_kernel = c->n_items_host != c->M ? 1 : 0;
     if (c->fuse_II && !c->adjoint) {
         a.coefAk0 = c->coefAk[0];   // a^(0), formed by the step's start
-        a.part2 = c->part;
+        a.part2 = part_II(c);
     }
+    a.small = small_args(c);
+    a.ex_next = c->ex[c->exc ^ 1];
     if (c->ws_stride > 0 && c->ws_feat && !c->adjoint) {   // record training pairs of this step
         a.rec.feat = c->ws_feat;
         a.rec.targ = c->ws_targ;
@@ -523,7 +561,37 @@ struct IIView {
     ItemList items_commit; // ... indexed by the item list of the order it left
 };
 
+// Arguments of the field updates on a small grid.
+void set_small_II(ecpic_ctx *c, const IIView &v) {
+    SmallII f{};
+    if (c->part_stride > 0) {
+        f.items = v.items;
+        f.items0 = v.fused ? v.items_commit : v.items;
+        f.wide0 = v.fused ? 1 : 0;
+        for (int b = 0; b < 2; ++b) f.part[b] = part_II(c, b);
+        f.taps = c->tapsA;
+        f.ntaps = c->ntA;
+        f.mlo = c->mloA;
+        f.E0y = c->E0y;
+        f.E0z = c->E0z;
+        f.eyn = c->ey[c->trc];
+        f.ezn = c->ez[c->trc];
+        f.ayn = c->ay[c->trc];
+        f.azn = c->az[c->trc];
+        f.ey0 = c->eyk[0];
+        f.ey1 = c->eyk[1];
+        f.ez0 = c->ezk[0];
+        f.ez1 = c->ezk[1];
+        f.coef = c->dt * c->w / c->dx;
+        f.half_dt = 0.5 * c->dt;
+        f.M = c->M;
+        f.wpi = c->block / 64;
+    }
+    c->smallII = f;
+}
+
 void enqueue_iters_II(ecpic_ctx *c, const IIView &v, int count) {
+    set_small_II(c, v);
     SweepIIArgs a{};
     a.xi = v.xi;
     a.p = v.p;
@@ -531,12 +599,12 @@ void enqueue_iters_II(ecpic_ctx *c, const IIView &v, int count) {
     a.coefAn = c->coefA;   // a_perp^n: Subsystem I leaves it alone
     a.coefAk0 = c->coefAk[0];
     a.coefAk1 = c->coefAk[1];
-    a.part = c->part;
+    a.part = part_II(c);
     a.st = c->stII;
     a.tol = c->tol;
     FieldIIArgs f{};
     f.items = v.items;
-    f.part = c->part;
+    f.part = part_II(c);
     f.taps = c->tapsA;
     f.ntaps = c->ntA;
     f.mlo = c->mloA;
@@ -558,8 +626,16 @@ void enqueue_iters_II(ecpic_ctx *c, const IIView &v, int count) {
     f.M = c->M;
     f.wpi = c->block / 64;
     const int gridp = particle_grid(c, v.exact);
+    a.small = c->smallII;
+    const bool small = a.small.M > 0;
     for (int i = 0; i < count; ++i) {
         a.k = f.k = c->kII++;
+        if (small) {
+            if (a.k == 0 && v.fused) continue;   // the commit has deposited it
+            a.part = part_II(c, a.k);
+            timed(c, "sweep_II", [&] { launch_sweep_II(c->P, gridp, c->block, c->stream, a); });
+            continue;
+        }
         if (a.k == 0 && v.fused) {
             FieldIIArgs f0 = f;
             f0.items = v.items_commit;
@@ -575,9 +651,9 @@ void enqueue_iters_II(ecpic_ctx *c, const IIView &v, int count) {
 void enqueue_commit_II(ecpic_ctx *c) {
     const int t = c->trc, n = t ^ 1;
     timed(c, "commit_II", [&] {
-        launch_commit_II((c->M + 255) / 256, c->stream, c->stII, c->stI, c->hdev, c->ey[t], c->ez[t], c->ay[t], c->az[t],
+        launch_commit_II(c->P, (c->M + 255) / 256, c->stream, c->stII, c->stI, c->hdev, c->ey[t], c->ez[t], c->ay[t], c->az[t],
                          c->eyk[0], c->eyk[1], c->ezk[0], c->ezk[1], c->ey[n], c->ez[n], c->ay[n], c->az[n],
-                         0.5 * c->dt, c->M, c->kII, c->tol);
+                         0.5 * c->dt, c->M, c->kII, c->tol, c->smallII);
     });
 }
 
@@ -655,6 +731,7 @@ int finish_I(ecpic_ctx *c, bool *recommitted) {
 }
 
 int finish_II(ecpic_ctx *c, const IIView &v) {
+    set_small_II(c, v);
     while (true) {
         const DevStatus &s = c->h->II;
         if (s.flags) return flags_to_status(s.flags);
@@ -883,10 +960,19 @@ int alloc_all(ecpic_ctx *c) {
     }
     rc |= dalloc(&c->base, (size_t)c->max_items * 3);
     rc |= dalloc(&c->cbase, (size_t)c->M * 3);
-    rc |= dalloc(&c->wcnt, (size_t)c->max_items * (c->block / 64) * 3);
+    // On a small grid the field updates open the next kernels; the partials and counts then
+    // alternate between two buffers, and Subsystem II has a third.  The line (with one item
+    // per cell, as a rule): every block forms the whole field, so the work grows with the
+    // cells and their taps where a field kernel's does not.  A step with field kernels and
+    // without: 128 cells cubic with 31 particles a cell 118 and 93 us, with 470 133 and 115,
+    // with 3900 188 and 181, quintic 123 and 111; 100 cells quintic 139 and 120; but 199
+    // cells cubic 119 and 118, quintic 138 and 156, 256 cells cubic 127 and 135.
+    const size_t units = (size_t)c->max_items * (c->block / 64), pn = units * std::max(2 * (c->P + 3), c->P + 4);
+    c->part_stride = M <= SMALL_CELLS && c->max_items <= 2 * M ? pn : 0;
+    rc |= dalloc(&c->wcnt, units * 3 * (c->part_stride ? 2 : 1));
     rc |= dalloc(&c->nstart, (size_t)2 * M + 1);
     // per item and wave: Subsystem I P+4 values, Subsystem II 2 (P+1)
-    rc |= dalloc(&c->part, (size_t)c->max_items * (c->block / 64) * std::max(2 * (c->P + 3), c->P + 4));
+    rc |= dalloc(&c->part, pn * (c->part_stride ? 3 : 1));
     rc |= dalloc(&c->E0y, M); rc |= dalloc(&c->E0z, M);
     const size_t nrec = (size_t)(M + 2);
     rc |= dalloc(&c->coefA, nrec * 2 * (c->P + 1));
@@ -1061,7 +1147,8 @@ int ecpic_create(const ecpic_config *cfg, ecpic_ctx **out) {
         c->block = 64 * g.waves_per_item;
     } else {
         const double items = (double)g.M * std::max(1.0, std::ceil(ppc / c->chunk));
-        const int wpi = (int)std::min(4.0, std::max(1.0, std::ceil(4096.0 / items)));
+        const double rows = std::max(1.0, std::ceil(ppc / 64.0));
+        const int wpi = (int)std::min(std::min(4.0, rows), std::max(1.0, std::ceil(4096.0 / items)));
         c->block = 64 * wpi;
     }
     c->max_items = (int)(g.M + g.n_particles / c->chunk + 2);
@@ -1455,7 +1542,7 @@ int finish_symmetric(ecpic_ctx *c, int sA, const StepSnap &q, int gI, int gII, i
             if (!rc) rc = ecpic_substep_fields(c, dt, &b);
         } else {
             turned = c->h->II.committed && !c->h->II.flags;   // and with it the second III, and the closing start
-            IIView v{c->pb[c->cur].xi, c->pb[c->cur].p, c->items[c->icur], true, false, {}};
+            IIView v{c->pb[c->cur].xi, c->pb[c->cur].p, c->items[c->icur], true, true, c->items[c->icur ^ 1]};
             rc = finish_II(c, v);
             step_stats(c, nullptr, &b);
             if (!rc) {
@@ -1618,6 +1705,7 @@ void enqueue_join(ecpic_ctx *c, int j) {
     const DevStatus *stI = c->stI;
     DevStatus *mirror = c->hdev;
     const int nsw = c->kII;
+    const SmallII small = c->smallII;
     advance(c);
     set_slot(c, j + 1);
     c->kI = 0;
@@ -1628,7 +1716,7 @@ void enqueue_join(ecpic_ctx *c, int j) {
                          c->eyk[1], c->ezk[0], c->ezk[1], c->ey[n], c->ez[n], c->ay[n], c->az[n], nsw, c->tol,
                          c->ex[c->exc], c->dt, c->coefA, c->coefE[0], c->coefAk[0], c->m0row.data(),
                          c->krow.data(), r * r, c->dt / (c->dx * c->dx), c->tapsA, c->ntA, c->mloA, c->M, c->E0y,
-                         c->E0z);
+                         c->E0z, small);
     });
     enqueue_ws_table(c);
 }

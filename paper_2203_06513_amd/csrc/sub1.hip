@@ -17,6 +17,7 @@
 // piece; waves with no such step skip that code.
 #include <type_traits>
 
+#include "small.hpp"
 #include "sweep.hpp"
 
 namespace ecpic {
@@ -293,7 +294,147 @@ __device__ __forceinline__ QueueW queue_of_wave(double *base, int wid) {
     return QueueW{w, w + QCAP, w + 2 * QCAP, reinterpret_cast<int *>(w + 3 * QCAP)};
 }
 
-template <int P, bool SEIDEL, typename T, int START, bool ADJ, bool SPIN>
+// ---- small grids -------------------------------------------------------------
+// With few cells a launch is all latency: a sweep of 4000 particles takes 4.2 us and the
+// field kernel behind it 5.7, of which its arithmetic is 0.4.  On up to SMALL_CELLS cells
+// the field update of sweep k therefore opens the next kernel, sweep k + 1 or the commit:
+// every block reads all wave partials from the L2, with the status words, forms e^(k+1) on
+// all cells in LDS, and so knows the residual of sweep k itself (together 7.5 us).  One
+// more block (the last of the grid) takes no particles and does the bookkeeping: the
+// iterate, the status, at the commit the new order's cells.  Blocks have SMALL_THREADS
+// threads; the first waves take the particles.  The partials and mover counts alternate
+// between two buffers, as a sweep writes its own while other blocks still read those
+// before.  4000 particles on 128 cells, a step: 118 us with field kernels, 93 without (both
+// subsystems).
+struct SmallField {
+    double *en, *ep, *ew;   // LDS: e^n, e^(k), e^(k+1) of every cell
+    double rx, re;          // residual of sweep k
+    int flags;
+};
+
+__host__ __device__ inline size_t small_I_doubles(int P, const SmallI &f) {
+    return (size_t)f.M * (P + 4) + f.ntaps + (f.M + f.ntaps - 1) + 3 * (size_t)f.M;
+}
+
+// The field update of sweep k, by SMALL_THREADS threads (a cell a thread, then a cell a
+// quad of lanes for the convolution, as in the field kernel); lds: small_I_doubles.  It
+// ends with a barrier.
+static_assert(SMALL_CELLS <= SMALL_THREADS && SMALL_THREADS <= MAX_BLOCK, "a cell a thread");
+
+// What it reads first, loaded with the status words (one memory round trip).
+struct SmallLoads {
+    double v[SMALL_Q], tap, en, ep;
+};
+
+template <int P>
+__device__ __forceinline__ SmallLoads small_loads_I(const SmallI &f, int k) {
+    const int t = threadIdx.x, tc = min(t, f.M - 1) + HALO;
+    SmallLoads l;
+    l.tap = f.taps[min(t, f.ntaps - 1)];
+    l.en = f.en[tc];
+    l.ep = (k == 0 ? f.en : ((k & 1) ? f.ek1 : f.ek0))[tc];
+    cell_totals<UnitI<P>::N, true>((k & 1) ? f.part[1] : f.part[0], f.wpi, f.M, t, l.v);
+#pragma unroll
+    for (int q = 0; q < SMALL_Q; ++q) asm volatile("" ::"v"(l.v[q]));   // not sunk behind the status test
+    asm volatile("" ::"v"(l.tap), "v"(l.en), "v"(l.ep));
+    return l;
+}
+
+template <int P>
+__device__ __forceinline__ SmallField small_field_I(const SmallI &f, const SmallLoads &l, const ItemList &it,
+                                                    bool one_each, int k, double *lds) {
+    constexpr int N = UnitI<P>::N, B = SMALL_THREADS;
+    __shared__ double redx[B / WAVE], rede[B / WAVE];
+    __shared__ int redf[B / WAVE];
+    const int t = threadIdx.x, M = f.M, ntaps = f.ntaps, slen = M + ntaps - 1;
+    double *raw = lds, *tp = raw + M * N, *S = tp + ntaps, *en = S + slen, *ep = en + M, *ew = ep + M;
+    stage_totals<N, true>(raw, (k & 1) ? f.part[1] : f.part[0], it, one_each, f.wpi, M, l.v);
+    if (t < ntaps) tp[t] = l.tap;   // ntaps <= M
+    if (t < M) { en[t] = l.en; ep[t] = l.ep; }
+    __syncthreads();
+    SmallField r{en, ep, ew, 0.0, 0.0, 0};
+    if (t < M) {   // the current of cell t, at every place of the window that has it
+        r.rx = raw[t * N + P + 2];
+        r.flags = (int)raw[t * N + P + 3];
+        double sum = 0.0;
+#pragma unroll
+        for (int q = 0; q < P + 2; ++q) {   // cell t - 1 + q: slot P + 1 - q
+            int c = t - 1 + q;
+            c = c < 0 ? c + M : (c >= M ? c - M : c);
+            sum += raw[c * N + P + 1 - q];
+        }
+        const int i0 = t + f.mlo + ntaps - 1;   // in [0, 2 M)
+        for (int i = i0 >= M ? i0 - M : i0; i < slen; i += M) S[i] = sum;
+    }
+    __syncthreads();
+    const int ql = t & 3;
+    for (int j = t >> 2; j < M; j += B / 4) {
+        const double *Sq = S + j + ntaps - 1;
+        double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+        int i = ql;
+        for (; i + 12 < ntaps; i += 16) {
+            a0 = fma(tp[i], Sq[-i], a0);
+            a1 = fma(tp[i + 4], Sq[-i - 4], a1);
+            a2 = fma(tp[i + 8], Sq[-i - 8], a2);
+            a3 = fma(tp[i + 12], Sq[-i - 12], a3);
+        }
+        for (; i < ntaps; i += 4) a0 = fma(tp[i], Sq[-i], a0);
+        double conv = (a0 + a1) + (a2 + a3);
+        conv += dpp_d<0xB1>(conv);   // quad_perm [1,0,3,2]
+        conv += dpp_d<0x4E>(conv);   // quad_perm [2,3,0,1]
+        const double e = en[j] - f.w * conv;
+        if (ql == 0) {
+            ew[j] = e;
+            r.re = fmax(r.re, fabs(e - ep[j]));
+            if (!(fabs(e) < 1.0e300)) r.flags |= FLAG_NONFINITE;
+        }
+    }
+    r.re = wave_max_dpp(r.re);
+    r.rx = wave_max_dpp(r.rx);
+    r.flags = wave_or_bits<4>(r.flags);
+    if ((t & (WAVE - 1)) == 0) { rede[t / WAVE] = r.re; redx[t / WAVE] = r.rx; redf[t / WAVE] = r.flags; }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < B / WAVE; ++w) {
+        r.re = fmax(r.re, rede[w]);
+        r.rx = fmax(r.rx, redx[w]);
+        r.flags |= redf[w];
+    }
+    return r;
+}
+
+// The A-records of cells c-1, c, c+1, one value a thread (loaded before the field update
+// and put into LDS after it).
+template <int P>
+__device__ __forceinline__ double load_recA(const double *coefA, int c) {
+    constexpr int NA = RecA<P>::N;
+    return coefA[(size_t)(rec_index(c) - 1) * NA + min((int)threadIdx.x, 3 * NA - 1)];
+}
+
+// These and the E-records of ebar = (e^n + e)/2 into LDS; the caller synchronises.
+template <int P>
+__device__ __forceinline__ void stage_records_small(LdsRec<P, double> *rec, double ra, const double *en,
+                                                    const double *e, int c, int M) {
+    constexpr int NA = RecA<P>::N;
+    const int t = threadIdx.x;
+    if (t < 3 * NA) {
+        const int r = t / NA, i = t % NA;
+        if (i <= P) rec[r].ay[i] = ra;
+        else rec[r].az[i - P - 1] = ra;
+    }
+    const int q = t - 2 * WAVE;   // (3 NA <= 2 WAVE)
+    if (q >= 0 && q < 3) {
+        double v[P];
+        make_recE<P>([&](int j) {   // j in [-P, M]
+            const int jj = j < 0 ? j + M : (j >= M ? j - M : j);
+            return 0.5 * (en[jj] + e[jj]);
+        }, c - 1 + q, v);
+#pragma unroll
+        for (int i = 0; i < P; ++i) rec[q].eb[i] = v[i];
+    }
+}
+
+template <int P, bool SEIDEL, typename T, int START, bool ADJ, bool SPIN, bool SMALL>
 __device__ __forceinline__ void sweep_I_item(const SweepIArgs &a, int item, LdsRec<P, T> *rec, double *queue) {
     static_assert(!ADJ || SEIDEL, "the adjoint scheme deposits the increment it has just produced");
     static_assert(!SPIN || (sizeof(T) == 8 && START != START_FLOAT), "spin runs the plain FP64 sweeps");
@@ -303,16 +444,21 @@ __device__ __forceinline__ void sweep_I_item(const SweepIArgs &a, int item, LdsR
     const int k = a.k;
     // the item count, the status words and the item's description are loaded
     // together, so the start costs one memory round trip instead of three
-    const int n_items = *a.items.n_items;
+    const int n_items = a.items.n_items[0];
+    const bool one_each = SMALL && a.items.n_items[1] != 0;
     const int sgate = st->gate, sflags = st->flags, skconv = st->kconv;
     const unsigned long long rxb = st->rx_bits[(k - 1) & 1], reb = st->re_bits[(k - 1) & 1];
-    const int c = a.items.cell[item];
-    const int beg = a.items.begin[item], end = a.items.begin[item + 1];
+    const bool book = SMALL && blockIdx.x == gridDim.x - 1;   // the bookkeeping block of a small grid
+    if (book) item = 0;
+    const int c = book ? 0 : a.items.cell[item];   // (there may be no item)
+    const int beg = book ? 0 : a.items.begin[item], end = book ? 0 : a.items.begin[item + 1];
+    SmallLoads pre{};
+    if constexpr (SMALL) pre = small_loads_I<P>(a.small, k - 1);
     asm volatile("" ::"s"(n_items), "s"(sgate), "s"(sflags), "s"(skconv), "s"(rxb), "s"(reb), "s"(c), "s"(beg),
                  "s"(end));
-    if (item >= n_items) return;
+    if (item >= n_items && !book) return;
     if (!sgate | sflags | (skconv >= 0)) return;
-    if (F64 && prev_converged(st, k, a.first64, a.dx, a.tol, threadIdx.x == 0, rxb, reb)) return;
+    if (!SMALL && F64 && prev_converged(st, k, a.first64, a.dx, a.tol, threadIdx.x == 0, rxb, reb)) return;
     const T *din;
     T *dout;
     if constexpr (F64) {
@@ -331,7 +477,7 @@ __device__ __forceinline__ void sweep_I_item(const SweepIArgs &a, int item, LdsR
     // d^(0) is kept in FP64 where a Jacobi commit may take it
     constexpr bool keep_start = F64 && !SEIDEL && (explicit_start || from_float || from_prev);
     const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;
-    const int nw = blockDim.x / WAVE;
+    const int nw = SMALL ? a.small.wpi : (int)blockDim.x / WAVE;   // waves that take particles
     int wb, we;
     wave_range(beg, end, wid, nw, wb, we);
     // first row of this wave (clamped index: lanes past the run recompute its
@@ -350,8 +496,28 @@ __device__ __forceinline__ void sweep_I_item(const SweepIArgs &a, int item, LdsR
         else if constexpr (!explicit_start) nd = din[il];
         if constexpr (SPIN) { nsy = a.sy[il]; nsz = a.sz[il]; }
     }
-    stage_records<P, T>(rec, a.coefA, coefE, c);
+    if constexpr (SMALL) {
+        const double ra = load_recA<P>(a.coefA, c);
+        const SmallField f = small_field_I<P>(a.small, pre, a.items, one_each, k - 1, queue);
+        if (book) {
+            double *eo = (k & 1) ? a.small.ek1 : a.small.ek0;
+            for (int j = threadIdx.x; j < a.small.M; j += blockDim.x) store_padded(eo, a.small.M, j, f.ew[j]);
+            if (threadIdx.x == 0) {
+                if (f.flags & FLAG_QUEUED) st->queued = 1;
+                if (f.flags & FLAG_ERRORS) st->flags = f.flags & FLAG_ERRORS;
+                else prev_converged(st, k, a.first64, a.dx, a.tol, true, bitsd(f.rx), bitsd(f.re));
+            }
+            return;
+        }
+        if (f.flags & FLAG_ERRORS) return;
+        if (prev_converged(st, k, a.first64, a.dx, a.tol, false, bitsd(f.rx), bitsd(f.re))) return;
+        stage_records_small<P>(rec, ra, f.en, f.ew, c, a.small.M);
+        queue += small_I_doubles(P, a.small);
+    } else {
+        stage_records<P, T>(rec, a.coefA, coefE, c);
+    }
     __syncthreads();
+    if (SMALL && wid >= nw) return;
     Own<P, T> o1;
     own_from_lds<P, T>(rec, o1);
     // Every load issued so far (the first row, the records) completes here, so
@@ -558,11 +724,12 @@ __device__ __forceinline__ void sweep_I_item(const SweepIArgs &a, int item, LdsR
 // One kernel per start mode (the host knows it), so that each is allocated the
 // registers it needs rather than the most any mode needs.  ADJ: the adjoint
 // scheme (FP64, Seidel map, explicit start or read).
-template <int P, bool SEIDEL, typename T, int START, bool ADJ, bool SPIN = false>
+// SMALL: opens with the field update of the sweep before it (see small_field_I).
+template <int P, bool SEIDEL, typename T, int START, bool ADJ, bool SPIN = false, bool SMALL = false>
 __global__ void __launch_bounds__(MAX_BLOCK) k_sweep_I(SweepIArgs a) {
     __shared__ LdsRec<P, T> rec[3];   // cells c-1, c, c+1
-    extern __shared__ double queue[];   // the waves' queues (degree >= 4)
-    sweep_I_item<P, SEIDEL, T, START, ADJ, SPIN>(a, blockIdx.x, rec, queue);
+    extern __shared__ double queue[];   // the field's arrays (SMALL), the waves' queues (degree >= 4)
+    sweep_I_item<P, SEIDEL, T, START, ADJ, SPIN, SMALL>(a, blockIdx.x, rec, queue);
 }
 
 // Sum of the wave partials of cell c (its items times wpi waves each): the P+2
@@ -986,6 +1153,104 @@ __global__ void __launch_bounds__(1024) k_commit_list(CommitIArgs a) {
     }
 }
 
+// A cell's mover counts as loaded (one item per cell: summed once they have arrived; other
+// lists are followed then).
+struct Movers {
+    int v[MAX_WAVES][3], start;
+};
+
+__device__ __forceinline__ Movers load_movers(const ItemList &it, const int32_t *wcnt, int wpi, int cell) {
+    Movers m;
+    const int32_t *q = wcnt + (size_t)cell * wpi * 3;
+#pragma unroll
+    for (int w = 0; w < MAX_WAVES; ++w) {
+        const int ww = min(w, wpi - 1);
+        m.v[w][0] = q[3 * ww]; m.v[w][1] = q[3 * ww + 1]; m.v[w][2] = q[3 * ww + 2];
+    }
+    m.start = it.begin[cell];
+    return m;
+}
+
+__device__ __forceinline__ void sum_movers(const Movers &r, const ItemList &it, const int32_t *wcnt, int wpi,
+                                           bool one_each, int cell, int (&m)[3], int &start) {
+    if (!one_each) {
+        cell_movers(it, wcnt, wpi, nullptr, false, cell, false, m, start);
+        return;
+    }
+    start = r.start;
+    m[0] = m[1] = m[2] = 0;
+#pragma unroll
+    for (int w = 0; w < MAX_WAVES; ++w) {
+        const int u = w < wpi ? 1 : 0;
+        m[0] += u * r.v[w][0]; m[1] += u * r.v[w][1]; m[2] += u * r.v[w][2];
+    }
+}
+
+// The cell whose movers a thread loads: in the bookkeeping block its own, else (first wave)
+// lanes 0 .. 4 cells c-2 .. c+2, 5 and 6 cells 0 and M-1.
+__device__ __forceinline__ int mover_cell(bool book, int c, int M) {
+    const int t = threadIdx.x;
+    return book ? min(t, M - 1) : (t < 5 ? imod(c - 2 + t, M) : (t == 6 ? M - 1 : 0));
+}
+
+// Destinations of an item's first mover of each kind (what the field kernel leaves in
+// cbase and base), by the first wave: dst in LDS, the caller synchronises.
+__device__ __forceinline__ void cell_dest(const Movers &r, const ItemList &it, const int32_t *wcnt, int wpi,
+                                          bool one_each, int c, int item, int M, int *dst) {
+    const int t = threadIdx.x;
+    if (t >= WAVE) return;
+    int m[3] = {0, 0, 0}, start = 0;
+    if (t < 7) sum_movers(r, it, wcnt, wpi, one_each, mover_cell(false, c, M), m, start);
+    if (t == 7 && !one_each)   // the cell's items before this one
+        for (int u = it.cell_first[c] * wpi; u < item * wpi; ++u)
+            for (int q = 0; q < 3; ++q) m[q] += wcnt[u * 3 + q];
+    const int wrap = __shfl(m[2], 6) - __shfl(m[0], 5);   // R_{M-1} - L_0
+    int ns[3];                                            // new starts of cells c-1, c, c+1
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int v = __shfl(start, 1 + q) + __shfl(m[0], 1 + q) - __shfl(m[2], q) + wrap;
+        ns[q] = imod(c - 1 + q, M) == 0 ? 0 : v;
+    }
+    const int d0 = ns[0] + __shfl(m[2], 0) + __shfl(m[1], 1) + __shfl(m[0], 7);
+    const int d1 = ns[1] + __shfl(m[2], 1) + __shfl(m[1], 7);
+    const int d2 = ns[2] + __shfl(m[2], 7);
+    if (t == 0) { dst[0] = d0; dst[1] = d1; dst[2] = d2; }
+}
+
+// The bookkeeping block of a committing small grid: e_x^{n+1}, and the new order's cells
+// (what the field kernel leaves in nstart and the next item list).  Returns whether some
+// cell has other than one item.  tl: LDS, 4 ints a cell (the place of the partials, which
+// have been read).
+__device__ __forceinline__ int small_order(const CommitIArgs &a, const Movers &r, const int32_t *wcnt, bool one_each,
+                                           const double *e, int *tl, int *lds) {
+    const int c = threadIdx.x, M = a.M;
+    if (c < M) {
+        int m[3], start;
+        sum_movers(r, a.items, wcnt, a.wpi, one_each, c, m, start);
+        tl[4 * c] = m[0]; tl[4 * c + 1] = m[1]; tl[4 * c + 2] = m[2]; tl[4 * c + 3] = start;
+    }
+    if (c == 0) lds[0] = 0;
+    __syncthreads();
+    if (c < M) {
+        const int wrap = tl[4 * (M - 1) + 2] - tl[0];   // R_{M-1} - L_0
+        const int cm = c == 0 ? M - 1 : c - 1, cp = c == M - 1 ? 0 : c + 1;
+        const int ns = c == 0 ? 0 : tl[4 * c + 3] + tl[4 * c] - tl[4 * cm + 2] + wrap;
+        const int cnt = tl[4 * cm + 2] + tl[4 * c + 1] + tl[4 * cp];   // R_{c-1} + S_c + L_{c+1}
+        a.nstart[c] = ns;
+        a.nstart[M + 1 + c] = cnt;
+        a.items_next.cell[c] = c;
+        a.items_next.begin[c] = ns;
+        a.items_next.cell_first[c] = c;
+        store_padded(a.ex_next, M, c, e[c]);
+        if (items_of(cnt, a.chunk) != 1) lds[0] = 1;
+    }
+    __syncthreads();
+    const int multi = lds[0];
+    __syncthreads();
+    if (c == 0) a.st->scan_multi = multi;
+    return multi;
+}
+
 // Totals over the lanes of a wave of NV values per lane held in LDS, value u
 // of lane i at col[u * stride + i]; lane u < NV returns total u.  A lane sums
 // one value over a run of lanes (staggered, so that the lanes of a run read
@@ -1037,7 +1302,7 @@ __device__ __forceinline__ double wave_totals_lds(double *col, int stride, int l
 // sweep's delta^(kc+1); the momentum is the P that increment stands for (the
 // closed form of adjoint_momentum), so no push is evaluated again.  It forms no
 // Subsystem II deposit (the adjoint substep closes a step) and records nothing.
-template <int P, bool RECORD, bool ADJ, bool SPIN>
+template <int P, bool RECORD, bool ADJ, bool SPIN, bool SMALL>
 __device__ __forceinline__ void commit_scatter_item(const CommitIArgs &a, int item) {
     static_assert(!(ADJ && RECORD), "pairs are recorded from the scheme's own commit");
     static_assert(!(SPIN && RECORD), "the learned warm start runs without spin");
@@ -1045,46 +1310,100 @@ __device__ __forceinline__ void commit_scatter_item(const CommitIArgs &a, int it
     __shared__ LdsRec<P, double> rec[3];   // cells c-1, c, c+1
     __shared__ double rk[3][NA];           // a^(0) records of cells c-1, c, c+1 (part2)
     __shared__ int lds[16];
+    __shared__ int dst[3];                 // SMALL: destinations of the item's first mover of each kind
     extern __shared__ double mvl[];        // part2: per wave [left, right][y, z][P+1][64 lanes] mover moments
+                                           // (SMALL: before that the field's arrays)
     // item count, status words, the residual slots of the last sweep and the
     // item description in one memory round trip
     const int n_items = a.items.n_items[0], one_each = a.items.n_items[1];
     const int sgate = a.st->gate, sflags = a.st->flags, skconv = a.st->kconv, smulti = a.st->scan_multi;
     const unsigned long long rxb = a.st->rx_bits[(a.nsweeps - 1) & 1], reb = a.st->re_bits[(a.nsweeps - 1) & 1];
-    const int c = a.items.cell[item];
-    const int beg = a.items.begin[item], end = a.items.begin[item + 1];
+    const bool book = SMALL && blockIdx.x == gridDim.x - 1;   // the bookkeeping block of a small grid
+    if (book) item = 0;
+    const int c = book ? 0 : a.items.cell[item];   // (there may be no item)
+    const int beg = book ? 0 : a.items.begin[item], end = book ? 0 : a.items.begin[item + 1];
+    SmallLoads fl{};
+    if constexpr (SMALL) fl = small_loads_I<P>(a.small, a.nsweeps - 1);   // the sweep it most likely takes
     asm volatile("" ::"s"(n_items), "s"(one_each), "s"(sgate), "s"(sflags), "s"(skconv), "s"(smulti), "s"(rxb),
                  "s"(reb), "s"(c), "s"(beg), "s"(end));
     // the converged sweep: recorded by an earlier sweep's start, else the test
     // of the last enqueued sweep, made here by every block (block 0 records it)
     int kc = -1;
-    if (sgate && !sflags) {
-        kc = skconv;
-        if (kc < 0 && prev_converged(a.st, a.nsweeps, a.first64, a.dx, a.tol, item == 0 && threadIdx.x == 0, rxb, reb))
-            kc = a.nsweeps - 1;
-    }
-    if (item == 0) commit_finish(a, kc, smulti, lds);
-    if (item >= n_items || kc < 0) return;   // the commit runs on a converged, unflagged substep
-    const CommitPick pk = commit_pick(a, kc);
     const int M = a.M;
+    SmallField sf{};
+    const int32_t *wcnt = a.wcnt;
+    double nx = 0.0, np = 0.0, nd = 0.0;   // the next row, loaded before the current one is computed
+    double nsy = 0.0, nsz = 0.0;           // spin (SPIN)
+    int32_t nid = 0;
     const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;
-    const int nw = blockDim.x / WAVE;
+    const int nw = SMALL ? a.small.wpi : (int)blockDim.x / WAVE;   // waves that take particles
     int wb, we;
     wave_range(beg, end, wid, nw, wb, we);
-    stage_records<P, double>(rec, a.coefA, pk.coefE, c);
+    auto first_row = [&](const double *d) {
+        if (wb >= we) return;
+        const int il = min(wb + lane, we - 1);
+        nx = a.cur.xi[il];
+        np = a.cur.p[il];
+        nd = d[il];
+        nid = a.cur.id[il];
+        if constexpr (SPIN) { nsy = a.cur.sy[il]; nsz = a.cur.sz[il]; }
+    };
+    double ra = 0.0;
+    if constexpr (SMALL) {
+        if (item >= n_items && !book) return;
+        if (sgate && !sflags) {
+            const int k = skconv >= 0 ? skconv : a.nsweeps - 1;
+            wcnt = (k & 1) ? a.small.wcnt[1] : a.small.wcnt[0];
+            // what does not depend on the field update is loaded before it
+            if (k != a.nsweeps - 1) fl = small_loads_I<P>(a.small, k);
+            const Movers mv = load_movers(a.items, wcnt, a.wpi, mover_cell(book, c, M));
+            ra = load_recA<P>(a.coefA, c);
+            if (!book) first_row(commit_pick(a, k).d);
+            sf = small_field_I<P>(a.small, fl, a.items, one_each != 0, k, mvl);
+            const bool writer = book && threadIdx.x == 0;
+            if (sf.flags & FLAG_ERRORS) {
+                if (writer) a.st->flags = sf.flags & FLAG_ERRORS;
+            } else if (skconv >= 0 || prev_converged(a.st, a.nsweeps, a.first64, a.dx, a.tol, writer, bitsd(sf.rx),
+                                                     bitsd(sf.re))) {
+                kc = k;
+            }
+            if (writer && (sf.flags & FLAG_QUEUED)) a.st->queued = 1;
+            if (kc >= 0 && !book) cell_dest(mv, a.items, wcnt, a.wpi, one_each != 0, c, item, M, dst);
+            if (kc >= 0 && book) {
+                const int multi = small_order(a, mv, wcnt, one_each != 0, sf.ew, reinterpret_cast<int *>(mvl), lds);
+                commit_finish(a, kc, multi, lds);
+                return;
+            }
+        }
+        if (book) commit_finish(a, kc, 0, lds);
+        if (book || kc < 0) return;
+        __syncthreads();   // dst is complete
+    } else {
+        if (sgate && !sflags) {
+            kc = skconv;
+            if (kc < 0 &&
+                prev_converged(a.st, a.nsweeps, a.first64, a.dx, a.tol, item == 0 && threadIdx.x == 0, rxb, reb))
+                kc = a.nsweeps - 1;
+        }
+        if (item == 0) commit_finish(a, kc, smulti, lds);
+        if (item >= n_items || kc < 0) return;   // the commit runs on a converged, unflagged substep
+    }
+    const CommitPick pk = commit_pick(a, kc);
+    if constexpr (SMALL) stage_records_small<P>(rec, ra, sf.en, a.seidel ? sf.ew : sf.ep, c, M);
+    else stage_records<P, double>(rec, a.coefA, pk.coefE, c);
     const bool dep2 = a.part2 != nullptr;
     if (dep2)
         for (int t = threadIdx.x; t < 3 * NA; t += blockDim.x)
             (&rk[0][0])[t] = a.coefAk0[(size_t)(rec_index(c) - 1) * NA + t];
     const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (WAVE - lane));
-    const int32_t *cb = a.cbase + (size_t)c * 3;
+    const int32_t *cb = SMALL ? dst : a.cbase + (size_t)c * 3;
     int run0 = cb[0], run1 = cb[1], run2 = cb[2];
-    if (!one_each) {   // movers of the cell's earlier items
+    if (!SMALL && !one_each) {   // movers of the cell's earlier items
         const int32_t *bs = a.base + (size_t)item * 3;
         run0 += bs[0]; run1 += bs[1]; run2 += bs[2];
     }
-    for (int w = 0; w < wid; ++w) {   // movers of the item's earlier waves
-        const int32_t *n = a.wcnt + ((size_t)item * nw + w) * 3;
+    for (int w = 0; w < min(wid, nw); ++w) {   // movers of the item's earlier waves
+        const int32_t *n = wcnt + ((size_t)item * nw + w) * 3;
         run0 += n[0]; run1 += n[1]; run2 += n[2];
     }
     int flags = 0;
@@ -1101,18 +1420,7 @@ __device__ __forceinline__ void commit_scatter_item(const CommitIArgs &a, int it
     if (dep2)
 #pragma unroll
         for (int u = 0; u < NM; ++u) col[u * WAVE + lane] = 0.0;
-    // the next row's loads are issued before the current row is computed
-    double nx = 0.0, np = 0.0, nd = 0.0;
-    double nsy = 0.0, nsz = 0.0;   // spin (SPIN)
-    int32_t nid = 0;
-    if (wb < we) {
-        const int il = min(wb + lane, we - 1);
-        nx = a.cur.xi[il];
-        np = a.cur.p[il];
-        nd = pk.d[il];
-        nid = a.cur.id[il];
-        if constexpr (SPIN) { nsy = a.cur.sy[il]; nsz = a.cur.sz[il]; }
-    }
+    if constexpr (!SMALL) first_row(pk.d);
     __builtin_amdgcn_s_waitcnt(0);
     for (int r0 = wb; r0 < we; r0 += WAVE) {
         const int i = r0 + lane;
@@ -1264,7 +1572,7 @@ __device__ __forceinline__ void commit_scatter_item(const CommitIArgs &a, int it
 #pragma unroll
             for (int j = 0; j <= P; ++j) out += in ? Bp.c[mm][j] * (comp == 0 ? ty[d][j] : tz[d][j]) : 0.0;
         }
-        if (lane < 2 * NW) a.part2[((size_t)item * nw + wid) * 2 * NW + lane] = out;
+        if (lane < 2 * NW && wid < nw) a.part2[((size_t)item * nw + wid) * 2 * NW + lane] = out;
     }
     if (flags && lane == 0) atomicOr(&a.st->flags, flags);   // flags is wave-uniform (wave_flag)
 }
@@ -1273,15 +1581,24 @@ __device__ __forceinline__ void commit_scatter_item(const CommitIArgs &a, int it
 // step enqueued ahead is only known on the device) and the extra blocks exit.
 // RECORD: the step also writes training pairs of the learned warm start (a
 // kernel of its own, so the plain one keeps its registers).
-template <int P, bool RECORD, bool ADJ, bool SPIN = false>
+// SMALL: opens with the field update of the last sweep (see small_field_I).
+template <int P, bool RECORD, bool ADJ, bool SPIN = false, bool SMALL = false>
 __global__ void __launch_bounds__(MAX_BLOCK) k_commit_scatter(CommitIArgs a) {
-    commit_scatter_item<P, RECORD, ADJ, SPIN>(a, blockIdx.x);
+    commit_scatter_item<P, RECORD, ADJ, SPIN, SMALL>(a, blockIdx.x);
 }
 
 
 // ---- launchers ------------------------------------------------------------
 template <int P, bool SEIDEL, typename T, bool ADJ, bool SPIN>
 void launch_sweep_mode(const SweepIArgs &a, int grid, int block, size_t lds, hipStream_t s) {
+    if constexpr (sizeof(T) == 8) {
+        if (a.small.M > 0 && a.k > 0) {   // opens with the field update: one block more
+            const size_t more = sizeof(double) * small_I_doubles(P, a.small);
+            launch_k((k_sweep_I<P, SEIDEL, T, START_READ, ADJ, SPIN, true>), dim3(grid + 1), dim3(SMALL_THREADS),
+                     more + (P >= 4 ? queue_lds_bytes(SMALL_THREADS) : 0), s, a);
+            return;
+        }
+    }
     if (a.k == 0 && a.explicit_start)
         launch_k((k_sweep_I<P, SEIDEL, T, START_EXPLICIT, ADJ, SPIN>), dim3(grid), dim3(block), lds, s, a);
     else if (!ADJ && a.k == 0 && a.dprev)
@@ -1342,6 +1659,23 @@ void launch_prep_records(int P, hipStream_t s, DevStatus *st, const double *ay, 
 void launch_commit_I(int P, bool adj, int grid, int block, hipStream_t s, const CommitIArgs &a) {
     const size_t lds = (a.part2 && !adj) ? sizeof(double) * 4 * (P + 1) * (size_t)block : 0;   // mover moments
     const bool spin = a.cur.sx != nullptr;
+    if (a.small.M > 0) {   // opens with the field update: one block more
+#define ECPIC_CS(PP)                                                                                               \
+    case PP: {                                                                                                      \
+        const size_t mv = a.part2 && !adj ? sizeof(double) * 4 * (PP + 1) * SMALL_THREADS : 0;                      \
+        const size_t all = std::max(mv, sizeof(double) * small_I_doubles(PP, a.small));                             \
+        const dim3 g(grid + 1), b(SMALL_THREADS);                                                                   \
+        if (adj && spin) launch_k((k_commit_scatter<PP, false, true, true, true>), g, b, all, s, a);                \
+        else if (adj) launch_k((k_commit_scatter<PP, false, true, false, true>), g, b, all, s, a);                  \
+        else if (spin) launch_k((k_commit_scatter<PP, false, false, true, true>), g, b, all, s, a);                 \
+        else launch_k((k_commit_scatter<PP, false, false, false, true>), g, b, all, s, a);                          \
+        break;                                                                                                      \
+    }
+        switch (P) { ECPIC_CS(2) ECPIC_CS(3) ECPIC_CS(4) ECPIC_CS(5) }
+#undef ECPIC_CS
+        if (a.list_kernel) launch_k(k_commit_list, dim3(1), dim3(1024), 0, s, a);
+        return;
+    }
 #define ECPIC_C(PP)                                                                                     \
     case PP:                                                                                            \
         if (adj) {                                                                                      \

@@ -18,6 +18,7 @@
 #include <cstddef>
 
 #include "coef.hpp"
+#include "small.hpp"
 
 namespace ecpic {
 
@@ -33,6 +34,160 @@ __device__ __forceinline__ bool prev_converged2(DevStatus *st, int k, double tol
     return false;
 }
 
+// ---- small grids -------------------------------------------------------------
+// As in Subsystem I (small_field_I): the field update of iterate k opens the next particle
+// pass, the commit or the join, each of whose blocks forms e^(k+1) on all cells and knows
+// the residual.  One block more than the items need does a pass's bookkeeping.
+struct SmallField2 {
+    double *y, *z;     // LDS: e^(k+1) of every cell
+    double *by, *bz;   // LDS: a^n - dt/2 e^n, the part of a^(k+1) that e^(k+1) does not enter
+    double re;
+    int flags;
+};
+
+__host__ __device__ inline size_t small_II_doubles(int P, const SmallII &f) {
+    return (size_t)f.M * 2 * (P + 3) + f.ntaps + 2 * (size_t)(f.M + f.ntaps - 1) + 4 * (size_t)f.M;
+}
+
+// What it reads first, loaded with the status words.
+struct SmallLoads2 {
+    double v[SMALL_Q], tap, E0y, E0z, ey, ez, ay, az, ky, kz;
+    int one_each;
+};
+
+template <int P>
+__device__ __forceinline__ SmallLoads2 small_loads_II(const SmallII &f, int k) {
+    const int t = threadIdx.x, tc = min(t, f.M - 1), th = tc + HALO;
+    const double *part = (k & 1) ? f.part[1] : f.part[0];
+    SmallLoads2 l;
+    const bool wide = k == 0 && f.wide0;
+    l.one_each = (wide ? f.items0 : f.items).n_items[1];
+    l.tap = f.taps[min(t, f.ntaps - 1)];
+    l.E0y = f.E0y[tc]; l.E0z = f.E0z[tc];
+    l.ey = f.eyn[th]; l.ez = f.ezn[th];
+    l.ay = f.ayn[th]; l.az = f.azn[th];
+    l.ky = (k == 0 ? f.eyn : ((k & 1) ? f.ey1 : f.ey0))[th];
+    l.kz = (k == 0 ? f.ezn : ((k & 1) ? f.ez1 : f.ez0))[th];
+    if (wide) cell_totals<2 * (P + 3), false>(part, f.wpi, f.M, t, l.v);
+    else cell_totals<2 * (P + 1), false>(part, f.wpi, f.M, t, l.v);
+#pragma unroll
+    for (int q = 0; q < SMALL_Q; ++q) asm volatile("" ::"v"(l.v[q]));   // not sunk behind the status test
+    asm volatile("" ::"v"(l.tap), "v"(l.E0y), "v"(l.E0z), "v"(l.ey), "v"(l.ez));
+    asm volatile("" ::"v"(l.ay), "v"(l.az), "v"(l.ky), "v"(l.kz), "s"(l.one_each));
+    return l;
+}
+
+// The two deposits at cell t from the cells' totals (RL: cells a partial reaches to the
+// right of its V0 range).
+template <int P, int RL>
+__device__ __forceinline__ void small_deposit(const double *raw, int M, int t, double &sy, double &sz) {
+    constexpr int NC = P + 1 + 2 * RL, NS = 2 * NC;
+    sy = 0.0;
+    sz = 0.0;
+#pragma unroll
+    for (int r = 0; r <= P + 2 * RL; ++r) {   // cell t - RL + r: slot P + 2 RL - r
+        int c = t - RL + r;
+        c = c < 0 ? c + M : (c >= M ? c - M : c);
+        sy += raw[c * NS + P + 2 * RL - r];
+        sz += raw[c * NS + NC + P + 2 * RL - r];
+    }
+}
+
+// The field update of iterate k, by SMALL_THREADS threads; lds: small_II_doubles.  It ends
+// with a barrier.
+template <int P>
+__device__ __forceinline__ SmallField2 small_field_II(const SmallII &f, const SmallLoads2 &l, int k, double *lds) {
+    constexpr int B = SMALL_THREADS;
+    __shared__ double rede[B / WAVE];
+    __shared__ int redf[B / WAVE];
+    const int t = threadIdx.x, M = f.M, ntaps = f.ntaps, slen = M + ntaps - 1;
+    const bool wide = k == 0 && f.wide0;
+    double *raw = lds, *tp = raw + M * 2 * (P + 3), *Sy = tp + ntaps, *Sz = Sy + slen, *y = Sz + slen, *z = y + M,
+           *by = z + M, *bz = by + M;
+    const double *part = (k & 1) ? f.part[1] : f.part[0];
+    if (wide) stage_totals<2 * (P + 3), false>(raw, part, f.items0, l.one_each != 0, f.wpi, M, l.v);
+    else stage_totals<2 * (P + 1), false>(raw, part, f.items, l.one_each != 0, f.wpi, M, l.v);
+    if (t < ntaps) tp[t] = l.tap;   // ntaps <= M
+    if (t < M) {
+        by[t] = l.ay - f.half_dt * l.ey;
+        bz[t] = l.az - f.half_dt * l.ez;
+        y[t] = l.E0y;               // E0 until the convolution has been added
+        z[t] = l.E0z;
+    }
+    __syncthreads();
+    if (t < M) {
+        double sy, sz;
+        if (wide) small_deposit<P, 1>(raw, M, t, sy, sz);
+        else small_deposit<P, 0>(raw, M, t, sy, sz);
+        const int i0 = t + f.mlo + ntaps - 1;   // in [0, 2 M)
+        for (int i = i0 >= M ? i0 - M : i0; i < slen; i += M) { Sy[i] = sy; Sz[i] = sz; }
+    }
+    __syncthreads();
+    const int ql = t & 3;
+    for (int j = t >> 2; j < M; j += B / 4) {
+        const double *Syq = Sy + j + ntaps - 1, *Szq = Sz + j + ntaps - 1;
+        double cy = 0.0, cz = 0.0, cy1 = 0.0, cz1 = 0.0, cy2 = 0.0, cz2 = 0.0, cy3 = 0.0, cz3 = 0.0;
+        int i = ql;
+        for (; i + 12 < ntaps; i += 16) {
+            cy = fma(tp[i], Syq[-i], cy);
+            cz = fma(tp[i], Szq[-i], cz);
+            cy1 = fma(tp[i + 4], Syq[-i - 4], cy1);
+            cz1 = fma(tp[i + 4], Szq[-i - 4], cz1);
+            cy2 = fma(tp[i + 8], Syq[-i - 8], cy2);
+            cz2 = fma(tp[i + 8], Szq[-i - 8], cz2);
+            cy3 = fma(tp[i + 12], Syq[-i - 12], cy3);
+            cz3 = fma(tp[i + 12], Szq[-i - 12], cz3);
+        }
+        for (; i < ntaps; i += 4) {
+            cy = fma(tp[i], Syq[-i], cy);
+            cz = fma(tp[i], Szq[-i], cz);
+        }
+        cy = (cy + cy1) + (cy2 + cy3);
+        cz = (cz + cz1) + (cz2 + cz3);
+        cy += dpp_d<0xB1>(cy);
+        cz += dpp_d<0xB1>(cz);
+        cy += dpp_d<0x4E>(cy);
+        cz += dpp_d<0x4E>(cz);
+        if (ql == 0) {
+            y[j] += f.coef * cy;
+            z[j] += f.coef * cz;
+        }
+    }
+    __syncthreads();
+    SmallField2 r{y, z, by, bz, 0.0, 0};
+    if (t < M) {
+        r.re = fmax(fabs(y[t] - l.ky), fabs(z[t] - l.kz));
+        if (!(fabs(y[t]) < 1.0e300) || !(fabs(z[t]) < 1.0e300)) r.flags = FLAG_NONFINITE;
+    }
+    r.re = wave_max_dpp(r.re);
+    r.flags = __ballot(r.flags != 0) ? FLAG_NONFINITE : 0;
+    if ((t & (WAVE - 1)) == 0) { rede[t / WAVE] = r.re; redf[t / WAVE] = r.flags; }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < B / WAVE; ++w) {
+        r.re = fmax(r.re, rede[w]);
+        r.flags |= redf[w];
+    }
+    return r;
+}
+
+// The iterate that a commit behind nsweeps iterates takes (-1: none), with its field:
+// sgate .. skconv as read, l loaded for iterate nsweeps - 1; writer records the outcome.
+template <int P>
+__device__ __forceinline__ int small_settle_II(const SmallII &f, DevStatus *st, int nsweeps, double tol, bool writer,
+                                               int sgate, int sflags, int skconv, SmallLoads2 l, double *lds,
+                                               SmallField2 &sf) {
+    if (!sgate || sflags) return -1;
+    const int k = skconv >= 0 ? skconv : nsweeps - 1;
+    if (k != nsweeps - 1) l = small_loads_II<P>(f, k);
+    sf = small_field_II<P>(f, l, k, lds);
+    if (sf.flags) {
+        if (writer) st->flags = sf.flags;
+        return -1;
+    }
+    return skconv >= 0 || prev_converged2(st, nsweeps, tol, writer, bitsd(sf.re)) ? k : -1;
+}
+
 constexpr int SUB2_BATCH = 4;
 
 // The particle pass.  Each wave takes every nw-th row of 64 particles of the
@@ -40,7 +195,7 @@ constexpr int SUB2_BATCH = 4;
 // the current one (a row here is short work, shorter than a memory round
 // trip); it writes its own 2 (P+1) partial slots (V0 slot q <-> index
 // c - P + q, y then z).
-template <int P>
+template <int P, bool SMALL>
 __device__ __forceinline__ void sweep_II_item(const SweepIIArgs &a, int item) {
     constexpr int NA = RecA<P>::N;
     DevStatus *st = a.st;
@@ -49,14 +204,18 @@ __device__ __forceinline__ void sweep_II_item(const SweepIIArgs &a, int item) {
     const int n_items = *a.items.n_items;
     const int sgate = st->gate, sflags = st->flags, skconv = st->kconv;
     const unsigned long long reb = st->re_bits[(k - 1) & 1];
-    const int c = a.items.cell[item];
+    const bool book = SMALL && blockIdx.x == gridDim.x - 1;   // the bookkeeping block of a small grid
+    if (book) item = 0;
+    const int c = book ? 0 : a.items.cell[item];   // (there may be no item)
     const int beg = a.items.begin[item], end = a.items.begin[item + 1];
+    SmallLoads2 pre{};
+    if constexpr (SMALL) pre = small_loads_II<P>(a.small, k - 1);
     asm volatile("" ::"s"(n_items), "s"(sgate), "s"(sflags), "s"(skconv), "s"(reb), "s"(c), "s"(beg), "s"(end));
-    if (item >= n_items) return;
+    if (item >= n_items && !book) return;
     if (!sgate | sflags | (skconv >= 0)) return;
-    if (prev_converged2(st, k, a.tol, threadIdx.x == 0, reb)) return;
+    if (!SMALL && prev_converged2(st, k, a.tol, threadIdx.x == 0, reb)) return;
     const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;
-    const int nw = blockDim.x / WAVE;
+    const int nw = SMALL ? a.small.wpi : (int)blockDim.x / WAVE;   // waves that take particles
     const int stride = nw * WAVE;
     const int last = end - 1;   // items are never empty; loads past the run re-read it
     const int first = beg + wid * WAVE;
@@ -67,14 +226,53 @@ __device__ __forceinline__ void sweep_II_item(const SweepIIArgs &a, int item) {
 #pragma unroll
     for (int b = 0; b < SUB2_BATCH; ++b) {
         const int il = min(first + b * stride + lane, last);
-        xn[b] = a.xi[il];
-        pn[b] = a.p[il];
+        xn[b] = book ? 0.0 : a.xi[il];
+        pn[b] = book ? 0.0 : a.p[il];
     }
     const double *rn = a.coefAn + (size_t)rec_index(c) * NA;
     const double *rk = ((k & 1) ? a.coefAk1 : a.coefAk0) + (size_t)rec_index(c) * NA;
     double cn[NA], ck[NA];
+    if constexpr (SMALL) {
+        extern __shared__ double lds2[];
+        __shared__ double rec[NA];   // the record of a^(k) on the cell
 #pragma unroll
-    for (int i = 0; i < NA; ++i) { cn[i] = rn[i]; ck[i] = rk[i]; }
+        for (int i = 0; i < NA; ++i) cn[i] = rn[i];
+        const SmallField2 sf = small_field_II<P>(a.small, pre, k - 1, lds2);
+        if (book) {
+            double *yo = (k & 1) ? a.small.ey1 : a.small.ey0, *zo = (k & 1) ? a.small.ez1 : a.small.ez0;
+            const int j = threadIdx.x, M = a.small.M;
+            if (j < M) {
+                store_padded(yo, M, j, sf.y[j]);
+                store_padded(zo, M, j, sf.z[j]);
+            }
+            if (j == 0) {
+                if (sf.flags) st->flags = sf.flags;
+                else prev_converged2(st, k, a.tol, true, bitsd(sf.re));
+            }
+            return;
+        }
+        if (sf.flags || prev_converged2(st, k, a.tol, false, bitsd(sf.re))) return;
+        if (threadIdx.x < NA) {
+            constexpr Pieces<P> B{};
+            const int i = threadIdx.x % (P + 1);
+            const bool isz = (int)threadIdx.x > P;
+            double s = 0.0;
+#pragma unroll
+            for (int m = 0; m <= P; ++m) {
+                const int u = c - m < 0 ? c - m + a.small.M : c - m;
+                const double e = isz ? sf.z[u] : sf.y[u], b = isz ? sf.bz[u] : sf.by[u];
+                s += (b - a.small.half_dt * e) * B.c[m][i];
+            }
+            rec[threadIdx.x] = s;
+        }
+        __syncthreads();
+        if (wid >= nw) return;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) ck[i] = rec[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) { cn[i] = rn[i]; ck[i] = rk[i]; }
+    }
     double my[P + 1], mz[P + 1];
 #pragma unroll
     for (int i = 0; i <= P; ++i) { my[i] = 0.0; mz[i] = 0.0; }
@@ -135,9 +333,10 @@ __device__ __forceinline__ void sweep_II_item(const SweepIIArgs &a, int item) {
 
 // One block per work item; the grid may exceed the item count (the count of a
 // step enqueued ahead is only known on the device) and the extra blocks exit.
-template <int P>
+// SMALL: opens with the field update of the iterate before it (see small_field_II).
+template <int P, bool SMALL = false>
 __global__ void __launch_bounds__(MAX_BLOCK) k_sweep_II(SweepIIArgs a) {
-    sweep_II_item<P>(a, blockIdx.x);
+    sweep_II_item<P, SMALL>(a, blockIdx.x);
 }
 
 // Field iterate k+1 of Subsystem II and the A-records of a^(k+1).  Block b
@@ -525,9 +724,10 @@ struct JoinArgs {
     const double *taps;
     double half_dt, tol;
     int nsweeps;
+    SmallII small;                         // joins compiled to open with the field update
 };
 
-template <int P>
+template <int P, bool SMALL>
 __global__ void __launch_bounds__(256) k_step_join(JoinArgs g, StepStart a) {
     extern __shared__ double R[];
     DevStatus *st = g.st;
@@ -552,7 +752,12 @@ __global__ void __launch_bounds__(256) k_step_join(JoinArgs g, StepStart a) {
     asm volatile("" ::"v"(w_ay), "v"(w_az), "v"(w_ey), "v"(w_ez), "v"(w_tp), "v"(w_ex));
     asm volatile("" ::"v"(w_y0), "v"(w_y1), "v"(w_z0), "v"(w_z1));
     int kc = -1;
-    if (sgate && !sflags) {
+    SmallField2 sf{};
+    if constexpr (SMALL) {
+        const SmallLoads2 pre = small_loads_II<P>(g.small, g.nsweeps - 1);   // the iterate it most likely takes
+        kc = small_settle_II<P>(g.small, st, g.nsweeps, g.tol, blockIdx.x == 0 && t == 0, sgate, sflags, skconv, pre,
+                                R + step_start_lds(P, ntaps) / sizeof(double), sf);
+    } else if (sgate && !sflags) {
         kc = skconv;
         if (kc < 0 && prev_converged2(st, g.nsweeps, g.tol, blockIdx.x == 0 && t == 0, reb)) kc = g.nsweeps - 1;
     }
@@ -569,7 +774,8 @@ __global__ void __launch_bounds__(256) k_step_join(JoinArgs g, StepStart a) {
     const bool odd = ((kc + 1) & 1) != 0;
     auto commit_cell = [&](int idx, double ay, double az, double ey, double ez, double y0, double y1, double z0,
                            double z1) {
-        const double ny = odd ? y1 : y0, nz = odd ? z1 : z0;
+        const int js = SMALL ? imod(wlo + idx, M) : 0;
+        const double ny = SMALL ? sf.y[js] : (odd ? y1 : y0), nz = SMALL ? sf.z[js] : (odd ? z1 : z0);
         const double na_y = fma(-g.half_dt, ey + ny, ay), na_z = fma(-g.half_dt, ez + nz, az);
         Way[idx] = na_y; Waz[idx] = na_z; Wey[idx] = ny; Wez[idx] = nz;
         const int q = idx - (mhi + P);   // own cell j0 + q
@@ -605,13 +811,15 @@ __global__ void __launch_bounds__(256) k_conv(const double *in, double *out, con
 
 // Commit of Subsystem II: e_perp^{n+1} = e^(kc+1), a^{n+1} = a^n - dt/2 (e^n + e^{n+1}).
 // Every block settles the convergence test on its own (same answer); block 0
-// records the commit.  Running it again is harmless (same writes).
+// records the commit.  Running it again is harmless (same writes).  P > 0: opens with the
+// field update of a small grid of that degree (one block).
+template <int P>
 __global__ void __launch_bounds__(256) k_commit_II(DevStatus *st, const DevStatus *stI, DevStatus *mirror,
                                                    const double *eyn, const double *ezn, const double *ayn,
                                                    const double *azn, const double *ey0, const double *ey1,
                                                    const double *ez0, const double *ez1, double *ey_next,
                                                    double *ez_next, double *ay_next, double *az_next, double half_dt,
-                                                   int M, int nsweeps, double tol) {
+                                                   int M, int nsweeps, double tol, SmallII small) {
     // one memory round trip: the status words, the last residual and this
     // cell's fields, with both candidates for e^(kc+1) (which one depends only
     // on the parity of kc)
@@ -623,7 +831,12 @@ __global__ void __launch_bounds__(256) k_commit_II(DevStatus *st, const DevStatu
     const double y0 = ey0[jj], y1 = ey1[jj], z0 = ez0[jj], z1 = ez1[jj];
     const double ay = ayn[jj], az = azn[jj], ey = eyn[jj], ez = ezn[jj];
     int kc = -1;
-    if (sgate && !sflags) {
+    SmallField2 sf{};
+    if constexpr (P > 0) {
+        extern __shared__ double lds2[];
+        const SmallLoads2 pre = small_loads_II<P>(small, nsweeps - 1);
+        kc = small_settle_II<P>(small, st, nsweeps, tol, threadIdx.x == 0, sgate, sflags, skconv, pre, lds2, sf);
+    } else if (sgate && !sflags) {
         kc = skconv;
         if (kc < 0 && prev_converged2(st, nsweeps, tol, blockIdx.x == 0 && threadIdx.x == 0, reb)) kc = nsweeps - 1;
     }
@@ -631,7 +844,7 @@ __global__ void __launch_bounds__(256) k_commit_II(DevStatus *st, const DevStatu
         if (blockIdx.x == 0 && threadIdx.x == 0) st->committed = 1;
         if (j < M) {
             const bool odd = ((kc + 1) & 1) != 0;
-            const double ny = odd ? y1 : y0, nz = odd ? z1 : z0;
+            const double ny = P > 0 ? sf.y[j] : (odd ? y1 : y0), nz = P > 0 ? sf.z[j] : (odd ? z1 : z0);
             store_padded(ey_next, M, j, ny);
             store_padded(ez_next, M, j, nz);
             store_padded(ay_next, M, j, fma(-half_dt, ey + ny, ay));
@@ -646,7 +859,13 @@ __global__ void __launch_bounds__(256) k_commit_II(DevStatus *st, const DevStatu
 }
 
 void launch_sweep_II(int P, int grid, int block, hipStream_t s, const SweepIIArgs &a) {
-#define ECPIC_S2(PP) case PP: launch_k((k_sweep_II<PP>), dim3(grid), dim3(block), 0, s, a); break;
+#define ECPIC_S2(PP)                                                                                           \
+    case PP:                                                                                                   \
+        if (a.small.M > 0 && a.k > 0)   /* opens with the field update: one block more */                      \
+            launch_k((k_sweep_II<PP, true>), dim3(grid + 1), dim3(SMALL_THREADS),                              \
+                     sizeof(double) * small_II_doubles(PP, a.small), s, a);                                    \
+        else launch_k((k_sweep_II<PP>), dim3(grid), dim3(block), 0, s, a);                                     \
+        break;
     switch (P) { ECPIC_S2(2) ECPIC_S2(3) ECPIC_S2(4) ECPIC_S2(5) }
 #undef ECPIC_S2
 }
@@ -694,9 +913,9 @@ void launch_step_join(int P, hipStream_t s, DevStatus *st, const DevStatus *stI,
                       double *ez_next, double *ay_next, double *az_next, int nsweeps, double tol,
                       const double *exn_next, double dt, double *coefA, double *coefE0, double *coefAk0,
                       const double *m0, const double *kr, double r2, double ck, const double *taps, int ntaps,
-                      int mlo, int M, double *E0y, double *E0z) {
+                      int mlo, int M, double *E0y, double *E0z, const SmallII &small) {
     JoinArgs g{st, stI, mirror, stI_next, eyn, ezn, ayn, azn, ey0, ey1, ez0, ez1, ey_next, ez_next, ay_next,
-               az_next, exn_next, taps, 0.5 * dt, tol, nsweeps};
+               az_next, exn_next, taps, 0.5 * dt, tol, nsweeps, small};
     StepStart a{};
     a.coefA = coefA; a.coefE0 = coefE0; a.coefAk0 = coefAk0; a.E0y = E0y; a.E0z = E0z;
     a.m0.half = P; a.kk.half = P;
@@ -704,7 +923,13 @@ void launch_step_join(int P, hipStream_t s, DevStatus *st, const DevStatus *stI,
     a.dt = dt; a.r2 = r2; a.ck = ck; a.do_II = 1; a.ntaps = ntaps; a.mlo = mlo; a.M = M;
     const int grid = (M + FIELD2_OUT - 1) / FIELD2_OUT;
     const size_t lds = step_start_lds(P, ntaps);
-#define ECPIC_J(PP) case PP: launch_k((k_step_join<PP>), dim3(grid), dim3(256), lds, s, g, a); break;
+#define ECPIC_J(PP)                                                                                            \
+    case PP:                                                                                                   \
+        if (small.M > 0)                                                                                       \
+            launch_k((k_step_join<PP, true>), dim3(grid), dim3(SMALL_THREADS),                                 \
+                     lds + sizeof(double) * small_II_doubles(PP, small), s, g, a);                             \
+        else launch_k((k_step_join<PP, false>), dim3(grid), dim3(256), lds, s, g, a);                          \
+        break;
     switch (P) { ECPIC_J(2) ECPIC_J(3) ECPIC_J(4) ECPIC_J(5) }
 #undef ECPIC_J
 }
@@ -714,12 +939,19 @@ void launch_conv(int grid, hipStream_t s, const double *in, double *out, const d
     launch_k(k_conv, dim3(grid), dim3(256), 0, s, in, out, taps, ntaps, mlo, alpha, M);
 }
 
-void launch_commit_II(int grid, hipStream_t s, DevStatus *st, const DevStatus *stI, DevStatus *mirror,
+void launch_commit_II(int P, int grid, hipStream_t s, DevStatus *st, const DevStatus *stI, DevStatus *mirror,
                       const double *eyn, const double *ezn, const double *ayn, const double *azn, const double *ey0,
                       const double *ey1, const double *ez0, const double *ez1, double *ey_next, double *ez_next,
-                      double *ay_next, double *az_next, double half_dt, int M, int nsweeps, double tol) {
-    launch_k(k_commit_II, dim3(grid), dim3(256), 0, s, st, stI, mirror, eyn, ezn, ayn, azn, ey0, ey1, ez0,
-                       ez1, ey_next, ez_next, ay_next, az_next, half_dt, M, nsweeps, tol);
+                      double *ay_next, double *az_next, double half_dt, int M, int nsweeps, double tol,
+                      const SmallII &small) {
+#define ECPIC_C2(PP)                                                                                           \
+    case PP:                                                                                                   \
+        launch_k((k_commit_II<PP>), dim3(grid), dim3(256), PP > 0 ? sizeof(double) * small_II_doubles(PP, small) : 0, \
+                 s, st, stI, mirror, eyn, ezn, ayn, azn, ey0, ey1, ez0, ez1, ey_next, ez_next, ay_next, az_next, \
+                 half_dt, M, nsweeps, tol, small);                                                             \
+        break;
+    switch (small.M > 0 ? P : 0) { ECPIC_C2(0) ECPIC_C2(2) ECPIC_C2(3) ECPIC_C2(4) ECPIC_C2(5) }
+#undef ECPIC_C2
 }
 
 }  // namespace ecpic
