@@ -80,6 +80,13 @@ public:
         return (hipError_t)err.load();
     }
 
+    // A small array from pinned memory to dst.
+    static hipError_t from_pinned(void *dst, const void *src, size_t bytes) {
+        if (!pageable(dst)) return hipMemcpy(dst, src, bytes, hipMemcpyDefault);
+        std::memcpy(dst, src, bytes);
+        return hipSuccess;
+    }
+
 private:
     static constexpr size_t SLOT = (size_t)2 << 20, MIN_BYTES = (size_t)8 << 20;
     static constexpr int SLOTS = 16, THREADS = 8;

@@ -64,7 +64,7 @@ void launch_gauss(hipStream_t s, const double *rho, const double *ex, const doub
                   double *r, unsigned long long *maxbits);
 void launch_poisson_rhs(hipStream_t s, const double *rho, int M, double dx, double *u);
 void launch_pad(hipStream_t s, const double *in, double *out, double alpha, int M);
-void launch_unpad(hipStream_t s, const double *in, double *out, int M);
+void launch_unpad5(hipStream_t s, const double *const *in, double *out, int j0, int n);
 void launch_init_particles(hipStream_t s, const double *x, const double *p, int64_t n, double L, double inv_dx,
                            int M, double *xi, double *pp, int32_t *key, int32_t *val);
 void radix_sort(hipStream_t s, int32_t *k0, int32_t *v0, int32_t *k1, int32_t *v1, int64_t n, int key_bits,
@@ -194,6 +194,7 @@ struct Prof {
 }  // namespace
 
 namespace ecpic {
+constexpr int FIELDS_CELLS = 65536;   // cells of one piece of a field readout (2.6 MB of pinned memory)
 constexpr int STEP_BATCH = 16;   // steps enqueued before the host reads their statuses
 constexpr int MAX_WAVES_PER_ITEM = 4;
 thread_local LaunchEvents g_launch_events;
@@ -294,6 +295,7 @@ struct ecpic_ctx {
     double *epart = nullptr;        // [max_items] Zeeman sum per item
     std::vector<double> h_epart;
     HostCopy host_copy;             // large arrays to the caller's memory
+    double *h_fields = nullptr, *h_fields_dev = nullptr;   // pinned: the fields of up to FIELDS_CELLS cells read out
     Prof prof;
 };
 
@@ -910,6 +912,7 @@ void free_all(ecpic_ctx *c) {
     F(c->ws_pgrad); F(c->ws_ploss); F(c->ws_loss); F(c->ws_w2b);
     F(c->rho); F(c->rvec); F(c->uvec); F(c->out5); F(c->part_e); F(c->maxbits); F(c->count); F(c->cursor); F(c->ex_save);
     if (c->h_ring) hipHostFree(c->h_ring);
+    if (c->h_fields) hipHostFree(c->h_fields);
     c->host_copy.release();
     for (auto &e : c->prof.pool) hipEventDestroy(e);
     for (auto &pe : c->prof.pending) { hipEventDestroy(pe.second.first); hipEventDestroy(pe.second.second); }
@@ -998,6 +1001,10 @@ int alloc_all(ecpic_ctx *c) {
     if (rc) return ECPIC_ENOMEM;
     if (hipHostMalloc((void **)&c->h_ring, sizeof(*c->h_ring) * STEP_BATCH, hipHostMallocMapped) != hipSuccess)
         return ECPIC_ENOMEM;
+    if (hipHostMalloc((void **)&c->h_fields, sizeof(double) * 5 * std::min(M, FIELDS_CELLS), hipHostMallocMapped) !=
+            hipSuccess ||
+        hipHostGetDevicePointer((void **)&c->h_fields_dev, c->h_fields, 0) != hipSuccess)
+        return ECPIC_ENOMEM;
     if (hipHostGetDevicePointer((void **)&c->h_ring_dev, c->h_ring, 0) != hipSuccess) c->h_ring_dev = nullptr;
     set_slot(c, 0);
     // fields start at zero, items empty
@@ -1034,13 +1041,6 @@ int upload_padded(ecpic_ctx *c, const double *host, double *dev_pad) {
     }
     HIPCHK(hipMemcpyAsync(c->uvec, host, sizeof(double) * c->M, hipMemcpyHostToDevice, c->stream));
     launch_pad(c->stream, c->uvec, dev_pad, 1.0, c->M);
-    return sync(c);
-}
-
-int download_padded(ecpic_ctx *c, const double *dev_pad, double *host) {
-    if (!host) return ECPIC_OK;
-    launch_unpad(c->stream, dev_pad, c->rvec, c->M);
-    HIPCHK(hipMemcpyAsync(host, c->rvec, sizeof(double) * c->M, hipMemcpyDeviceToHost, c->stream));
     return sync(c);
 }
 
@@ -1214,17 +1214,14 @@ int ecpic_get_particles(ecpic_ctx *c, double *x, double *p, int64_t n) {
     if (!c || n != c->N || (n > 0 && (!x || !p))) return ECPIC_EINVAL;
     if (!c->have_particles) return ECPIC_ESTATE;
     hipSetDevice(c->device);
-    double *dx_ = nullptr, *dp_ = nullptr;
-    if (dalloc(&dx_, n) || dalloc(&dp_, n)) { if (dx_) hipFree(dx_); return ECPIC_ENOMEM; }
-    int rc = ecpic_get_particles_dev(c, dx_, dp_, n);
+    // the increments hold nothing between calls: room for the particles in their order
+    int rc = ecpic_get_particles_dev(c, c->dbuf[0], c->dbuf[1], n);
     if (rc == ECPIC_OK && n > 0) {
         const size_t bytes = sizeof(double) * (size_t)n;
-        if (c->host_copy.to_host(x, dx_, bytes, c->stream, c->device) != hipSuccess ||
-            c->host_copy.to_host(p, dp_, bytes, c->stream, c->device) != hipSuccess)
+        if (c->host_copy.to_host(x, c->dbuf[0], bytes, c->stream, c->device) != hipSuccess ||
+            c->host_copy.to_host(p, c->dbuf[1], bytes, c->stream, c->device) != hipSuccess)
             rc = ECPIC_EDEVICE;
     }
-    hipFree(dx_);
-    hipFree(dp_);
     return rc;
 }
 
@@ -1255,21 +1252,15 @@ int ecpic_get_spins(ecpic_ctx *c, double *sx, double *sy, double *sz, int64_t n)
     if (!c->have_particles) return ECPIC_ESTATE;
     hipSetDevice(c->device);
     if (n == 0) return ECPIC_OK;
-    double *t[3] = {nullptr, nullptr, nullptr};
-    if (dalloc(&t[0], n) || dalloc(&t[1], n) || dalloc(&t[2], n)) {
-        for (double *q : t) if (q) hipFree(q);
-        return ECPIC_ENOMEM;
-    }
-    const Particles &d = c->pb[c->cur];
-    launch_spin_out(c->stream, d.sx, d.sy, d.sz, d.id, n, t[0], t[1], t[2]);
-    int rc = ECPIC_OK;
+    // the spins of the other particle buffer hold nothing between calls
+    const Particles &d = c->pb[c->cur], &o = c->pb[c->cur ^ 1];
+    launch_spin_out(c->stream, d.sx, d.sy, d.sz, d.id, n, o.sx, o.sy, o.sz);
     double *out[3] = {sx, sy, sz};
-    for (int k = 0; k < 3 && rc == ECPIC_OK; ++k)
-        if (c->host_copy.to_host(out[k], t[k], sizeof(double) * (size_t)n, c->stream, c->device) != hipSuccess)
-            rc = ECPIC_EDEVICE;
-    if (rc == ECPIC_OK) rc = sync(c);
-    for (double *q : t) hipFree(q);
-    return rc;
+    const double *src[3] = {o.sx, o.sy, o.sz};
+    for (int k = 0; k < 3; ++k)
+        if (c->host_copy.to_host(out[k], src[k], sizeof(double) * (size_t)n, c->stream, c->device) != hipSuccess)
+            return ECPIC_EDEVICE;
+    return sync(c);
 }
 
 int ecpic_set_fields(ecpic_ctx *c, const double *ex, const double *ey, const double *ez, const double *ay,
@@ -1288,12 +1279,19 @@ int ecpic_set_fields(ecpic_ctx *c, const double *ex, const double *ey, const dou
 int ecpic_get_fields(ecpic_ctx *c, double *ex, double *ey, double *ez, double *ay, double *az) {
     if (!c) return ECPIC_EINVAL;
     hipSetDevice(c->device);
-    int rc = download_padded(c, c->ex[c->exc], ex);
-    if (!rc) rc = download_padded(c, c->ey[c->trc], ey);
-    if (!rc) rc = download_padded(c, c->ez[c->trc], ez);
-    if (!rc) rc = download_padded(c, c->ay[c->trc], ay);
-    if (!rc) rc = download_padded(c, c->az[c->trc], az);
-    return rc;
+    const double *src[5] = {c->ex[c->exc], c->ey[c->trc], c->ez[c->trc], c->ay[c->trc], c->az[c->trc]};
+    double *dst[5] = {ex, ey, ez, ay, az};
+    for (int j0 = 0; j0 < c->M; j0 += FIELDS_CELLS) {
+        const int n = std::min(FIELDS_CELLS, c->M - j0);
+        launch_unpad5(c->stream, src, c->h_fields_dev, j0, n);
+        const int rc = sync(c);
+        if (rc) return rc;
+        for (int q = 0; q < 5; ++q)
+            if (dst[q] &&
+                HostCopy::from_pinned(dst[q] + j0, c->h_fields + (size_t)q * n, sizeof(double) * n) != hipSuccess)
+                return ECPIC_EDEVICE;
+    }
+    return ECPIC_OK;
 }
 
 int ecpic_deposit_charge(ecpic_ctx *c, double *rho) {

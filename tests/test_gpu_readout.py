@@ -83,3 +83,45 @@ def test_2d_round_trip(n):
     for k, v in zip(("sx", "sy", "sz"), s):
         assert np.array_equal(gs[k], v)
     ctx.close()
+
+
+@pytest.mark.parametrize("warm", [0, 1])
+@pytest.mark.parametrize("splitting", [0, 1])
+def test_1d_readouts_between_steps(splitting, warm):
+    """Host readouts use buffers that hold nothing between calls: steps with readouts
+    between them are those without, bit for bit."""
+    n, L = 20000, 8.0
+    rng = np.random.default_rng(5)
+    x, p = rng.uniform(0, L, n), 0.1 * rng.normal(size=n)
+    s = [rng.normal(size=n) for _ in range(3)]
+    out = []
+    for read in (True, False):
+        ctx = ec.Context(L=L, M=150, degree=3, n_particles=n, dt=0.02, tol=1e-12, spin=True, hbar=0.01,
+                         splitting=splitting, warmstart=ec.WS_PREVIOUS if warm else ec.WS_EXPLICIT)
+        ctx.set_particles(x, p)
+        ctx.set_spins(*s)
+        ctx.solve_gauss()
+        for _ in range(3):
+            ctx.step(1)
+            if read:
+                ctx.get_particles()
+                ctx.get_spins()
+                ctx.get_fields()
+        out.append(ctx.state())
+        ctx.close()
+    for k in out[0]:
+        assert np.array_equal(out[0][k], out[1][k]), k
+
+
+@pytest.mark.parametrize("M", [8, 255, 256, 257, 65535, 65536, 65537, 131073])
+def test_1d_fields_round_trip(M):
+    """Fields come back in pieces of 65536 cells, as they were set."""
+    rng = np.random.default_rng(M)
+    ctx = ec.Context(L=1.0 * M, M=M, degree=3, n_particles=0, dt=0.01, tol=1e-12)
+    f = {k: rng.normal(size=M) for k in ("ex", "ey", "ez", "ay", "az")}
+    ctx.set_fields(**f)
+    for _ in range(2):
+        g = ctx.get_fields()
+        for k in f:
+            assert np.array_equal(g[k], f[k]), k
+    ctx.close()
