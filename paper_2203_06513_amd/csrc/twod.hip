@@ -1411,6 +1411,10 @@ struct DepArgs {
 
 // mode 1: S += w (A^n + A^(k)) / (gamma(p, A^n) + gamma(p, A^(k))) Lambda0(x_a),
 // with A^(k) the field of a^(k) = a^n - dt (e^n + e^(k)) / 2.
+// Bound by the LDS pipe: (P+1)^2 reads and (P+1)^2 atomics of 15 cycles a row, 115 us of
+// 512 x 512 cells with 2^24 cubic particles, and by its 40 bytes a particle (145 us).  The
+// patch's stride is a constant, so that the nodes are immediate offsets, and a row's loads
+// are issued a row ahead: 187 -> 167 us.
 template <int P>
 __global__ __launch_bounds__(BLOCK) void k2_deposit0(DepArgs a) {
     if (a.gate && *a.gate) return;   // uniform over the grid
@@ -1422,50 +1426,66 @@ __global__ __launch_bounds__(BLOCK) void k2_deposit0(DepArgs a) {
     const int r = tile / nseg, c0 = (tile - r * nseg) * a.TW;
     const int PC = a.TW + P;
     const int R0 = r - P, C0 = c0 - P;
+    const int begin = a.start[tile], end = a.start[tile + 1];
+    const int passes = (end - begin + WAVE - 1) / WAVE;   // none for an empty tile
+    const int nw = a.split * (BLOCK / WAVE);
+    int jr = part * (BLOCK / WAVE) + threadIdx.x / WAVE;
+    // a row's loads are issued a row ahead
+    double nu1 = 0.0, nu2 = 0.0, nq1 = 0.0, nq2 = 0.0, nA = 0.0;
+    auto load = [&](int row) {
+        if (row >= passes) return;
+        const int i = min(begin + row * WAVE + lane_id(), end - 1);
+        nu1 = a.xi1[i];
+        nu2 = a.xi2[i];
+        if (a.mode == 1) {
+            nq1 = a.p1[i];
+            nq2 = a.p2[i];
+            if (!a.first) nA = a.anp[i];
+        }
+    };
+    load(jr);
     for (int t = threadIdx.x; t < PR * PC; t += blockDim.x) {
         const int i = t / PC, j = t - i * PC;
         const int g = wrapi(R0 + i, a.M1) * a.M2 + wrapi(C0 + j, a.M2);
         if (a.mode == 1) {
             const double an = a.an[g];
-            if (a.first) sAn[t] = an;
-            sAk[t] = an - 0.5 * a.dt * (a.ezn[g] + a.ezk[g]);
+            if (a.first) sAn[i * PCM + j] = an;
+            sAk[i * PCM + j] = an - 0.5 * a.dt * (a.ezn[g] + a.ezk[g]);
         }
-        sS[t] = 0.0;
+        sS[i * PCM + j] = 0.0;
     }
     __syncthreads();
-    const int begin = a.start[tile], end = a.start[tile + 1];
-    const int passes = (end - begin + WAVE - 1) / WAVE;   // none for an empty tile
-    const int nw = a.split * (BLOCK / WAVE);
-    for (int jr = part * (BLOCK / WAVE) + threadIdx.x / WAVE; jr < passes; jr += nw) {
+    for (; jr < passes; jr += nw) {
         const int i = begin + jr * WAVE + lane_id();
         const bool live = i < end;
-        const int ii = live ? i : begin;
-        const double u1 = a.xi1[ii], u2 = a.xi2[ii];
+        const double u1 = nu1, u2 = nu2, q1 = nq1, q2 = nq2;
+        double An = nA;
+        load(jr + nw);
         const int c2 = (int)u2;
         double b1[P + 1], b2[P + 1];
         basis_values<P>(u1 - r, b1);
         basis_values<P>(u2 - c2, b2);
+        const int s0 = P * PCM + c2 - C0;   // node (r, c2) of the patch; (m1, m2) back from it
         double q = a.w;
         if (a.mode == 1) {
-            double An = 0.0, Ak = 0.0;
+            double An0 = 0.0, Ak = 0.0;
 #pragma unroll
             for (int m1 = 0; m1 <= P; ++m1) {
                 double tn = 0.0, tk = 0.0;
 #pragma unroll
                 for (int m2 = 0; m2 <= P; ++m2) {
-                    const int s = (r - m1 - R0) * PC + c2 - m2 - C0;
+                    const int s = s0 - m1 * PCM - m2;
                     if (a.first) tn += b2[m2] * sAn[s];
                     tk += b2[m2] * sAk[s];
                 }
-                An += b1[m1] * tn;
+                An0 += b1[m1] * tn;
                 Ak += b1[m1] * tk;
             }
             if (a.first) {
+                An = An0;
                 if (live) a.anp[i] = An;
-            } else {
-                An = a.anp[ii];
             }
-            const double q1 = a.p1[ii], q2 = a.p2[ii], pp = 1.0 + q1 * q1 + q2 * q2;
+            const double pp = 1.0 + q1 * q1 + q2 * q2;
             q = a.w * (An + Ak) * frcp(fsqrt(pp + An * An) + fsqrt(pp + Ak * Ak));
         }
         if (live) {
@@ -1473,7 +1493,7 @@ __global__ __launch_bounds__(BLOCK) void k2_deposit0(DepArgs a) {
             for (int m1 = 0; m1 <= P; ++m1) {
                 const double qb = q * b1[m1];
 #pragma unroll
-                for (int m2 = 0; m2 <= P; ++m2) atomicAdd(&sS[(r - m1 - R0) * PC + c2 - m2 - C0], qb * b2[m2]);
+                for (int m2 = 0; m2 <= P; ++m2) atomicAdd(&sS[s0 - m1 * PCM - m2], qb * b2[m2]);
             }
         }
     }
@@ -1481,7 +1501,7 @@ __global__ __launch_bounds__(BLOCK) void k2_deposit0(DepArgs a) {
     for (int t = threadIdx.x; t < PR * PC; t += blockDim.x) {
         const int i = t / PC, j = t - i * PC;
         const int g = wrapi(R0 + i, a.M1) * a.M2 + wrapi(C0 + j, a.M2);
-        if (sS[t] != 0.0) atomicAdd(&a.S[g], sS[t]);
+        if (sS[i * PCM + j] != 0.0) atomicAdd(&a.S[g], sS[i * PCM + j]);
     }
 }
 

@@ -1,5 +1,5 @@
-"""Large readouts go to the host through a pinned ring: 2 MiB slots, 16 of them, from 8 MiB
-up.  On the device the particles return to their order in two passes past 2^24 of them.
+"""Large readouts go to the host through a pinned ring of 16 slots, from 3 MiB up, in pieces
+of 0.5 to 2 MiB.  On the device the particles return to their order in two passes past 2^24 of them.
 
 Tolerance: momenta and spins are stored and returned as given, so they are equal bit by
 bit; steps are deterministic; positions pass through cell units (one product each way), hence a few ulp of L.
@@ -13,9 +13,13 @@ from workloads.twod import get2d
 pytestmark = pytest.mark.gpu
 
 SLOT = 2 << 17                 # doubles of a 2 MiB slot
-SIZES = [4 * SLOT - 1,         # below the ring's smallest size: the plain copy
-         4 * SLOT,             # whole slots only
-         4 * SLOT + 1,         # a last slot of one value
+SIZES = [3 * SLOT // 2 - 1,    # below the ring's smallest size: the plain copy
+         3 * SLOT // 2,        # six of the smallest pieces
+         3 * SLOT // 2 + 1,    # a last piece of one value
+         4 * SLOT - 1,
+         4 * SLOT,
+         4 * SLOT + 1,
+         8 * SLOT + 12345,     # pieces of 1 MiB
          16 * SLOT,            # each slot once
          35 * SLOT + 77]       # slots filled again
 
