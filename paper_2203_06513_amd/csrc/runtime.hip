@@ -911,7 +911,6 @@ void free_all(ecpic_ctx *c) {
     F(c->ws_theta); F(c->ws_m); F(c->ws_v); F(c->ws_norm); F(c->ws_table); F(c->ws_feat); F(c->ws_targ);
     F(c->ws_pgrad); F(c->ws_ploss); F(c->ws_loss); F(c->ws_w2b);
     F(c->rho); F(c->rvec); F(c->uvec); F(c->out5); F(c->part_e); F(c->maxbits); F(c->count); F(c->cursor); F(c->ex_save);
-    if (c->h_ring) hipHostFree(c->h_ring);
     if (c->h_fields) hipHostFree(c->h_fields);
     c->host_copy.release();
     for (auto &e : c->prof.pool) hipEventDestroy(e);
@@ -971,7 +970,7 @@ int alloc_all(ecpic_ctx *c) {
     // with 3900 188 and 181, quintic 123 and 111; 100 cells quintic 139 and 120; but 199
     // cells cubic 119 and 118, quintic 138 and 156, 256 cells cubic 127 and 135.
     const size_t units = (size_t)c->max_items * (c->block / 64), pn = units * std::max(2 * (c->P + 3), c->P + 4);
-    c->part_stride = M <= SMALL_CELLS && c->max_items <= 2 * M ? pn : 0;
+    c->part_stride = N > 0 && M <= SMALL_CELLS && c->max_items <= 2 * M ? pn : 0;
     rc |= dalloc(&c->wcnt, units * 3 * (c->part_stride ? 2 : 1));
     rc |= dalloc(&c->nstart, (size_t)2 * M + 1);
     // per item and wave: Subsystem I P+4 values, Subsystem II 2 (P+1)
@@ -999,13 +998,14 @@ int alloc_all(ecpic_ctx *c) {
         rc |= dalloc(&c->epart, c->max_items);
     }
     if (rc) return ECPIC_ENOMEM;
-    if (hipHostMalloc((void **)&c->h_ring, sizeof(*c->h_ring) * STEP_BATCH, hipHostMallocMapped) != hipSuccess)
-        return ECPIC_ENOMEM;
-    if (hipHostMalloc((void **)&c->h_fields, sizeof(double) * 5 * std::min(M, FIELDS_CELLS), hipHostMallocMapped) !=
+    // pinned: the room for fields read out, then the mirrors
+    const size_t fbytes = sizeof(double) * 5 * std::min(M, FIELDS_CELLS);
+    if (hipHostMalloc((void **)&c->h_fields, fbytes + sizeof(*c->h_ring) * STEP_BATCH, hipHostMallocMapped) !=
             hipSuccess ||
         hipHostGetDevicePointer((void **)&c->h_fields_dev, c->h_fields, 0) != hipSuccess)
         return ECPIC_ENOMEM;
-    if (hipHostGetDevicePointer((void **)&c->h_ring_dev, c->h_ring, 0) != hipSuccess) c->h_ring_dev = nullptr;
+    c->h_ring = reinterpret_cast<ecpic_ctx::HostMirror *>(reinterpret_cast<char *>(c->h_fields) + fbytes);
+    c->h_ring_dev = reinterpret_cast<ecpic_ctx::HostMirror *>(reinterpret_cast<char *>(c->h_fields_dev) + fbytes);
     set_slot(c, 0);
     // fields start at zero, items empty
     for (int b = 0; b < 2; ++b) {

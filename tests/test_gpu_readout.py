@@ -129,3 +129,18 @@ def test_1d_fields_round_trip(M):
         for k in f:
             assert np.array_equal(g[k], f[k]), k
     ctx.close()
+
+
+@pytest.mark.parametrize("M1,M2", [(8, 8), (8, 512), (256, 256), (512, 128), (512, 256)])
+def test_2d_fields_round_trip(M1, M2):
+    """Fields come back as they were set: up to 65536 nodes through pinned memory, and past."""
+    rng = np.random.default_rng(M1 + M2)
+    ctx = ec.Context2D(L1=1.0 * M1, L2=1.0 * M2, M1=M1, M2=M2, degree=3, n_particles=0, dt=0.01, tol=1e-12)
+    n = M1 * M2
+    f = dict(e=rng.normal(size=2 * n), bz=rng.normal(size=n), ez=rng.normal(size=n), az=rng.normal(size=n))
+    ctx.set_fields(**f)
+    for _ in range(2):
+        g = ctx.get_fields()
+        for k in f:
+            assert np.array_equal(g[k], f[k]), k
+    ctx.close()
