@@ -1301,6 +1301,7 @@ struct Resort {
 
 __global__ __launch_bounds__(SORT_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k2_tile_resort(Resort a) {
     __shared__ int hist[NKEY], first[NKEY];   // particles of a key; their first rank
+    __shared__ int nstay;                     // particles expected to stay in their cell
     __shared__ double val[INVCAP];            // one output array of the tile, by new position
     const int T = tile_of_block();
     const int ob = a.told[T], nold = a.told[T + 1] - ob;
@@ -1347,9 +1348,10 @@ __global__ __launch_bounds__(SORT_THREADS) __attribute__((amdgpu_waves_per_eu(4)
         }
         first[2 * t0] = inc - v0 - v1;
         first[2 * t0 + 1] = inc - v1;
+        if (2 * t0 == NKEY / 2) nstay = inc - v0 - v1;
     }
     __syncthreads();
-    const int nin = first[NKEY / 2];   // particles expected to stay in their cell
+    const int nin = nstay;   // (first[] holds the direct path's cursors from here on)
     auto place = [&](int rank) { return rank < nin ? tile_pos(rank, nin) : nin + tile_pos(rank - nin, cnt - nin); };
     if (direct) {
         for (int q = t0; q < nsrc; q += nt) {
