@@ -240,7 +240,10 @@ struct ecpic_ctx {
     int exc = 0, trc = 0;
     double *ek[2]{};
     double *eyk[2]{}, *ezk[2]{};
-    double *E0y = nullptr, *E0z = nullptr;
+    // constant part of the Subsystem II iteration, of the step in the current slot: slots of
+    // odd and even index have their own, since the blocks of a join form the next step's
+    // while others may still read this one's (small grids)
+    double *E0[2]{}, *E0y = nullptr, *E0z = nullptr;
     double *coefA = nullptr, *coefE[2]{}, *coefAk[2]{};
     double *taps1 = nullptr, *tapsA = nullptr;
     int nt1 = 0, mlo1 = 0, ntA = 0, mloA = 0;
@@ -359,6 +362,8 @@ void set_slot(ecpic_ctx *c, int j) {
     c->stII = c->stI + 1;
     c->h = c->h_ring + j;
     c->hdev = c->h_ring_dev ? &c->h_ring_dev[j].I : nullptr;
+    c->E0y = c->E0[j & 1];
+    c->E0z = c->E0y + c->M;
 }
 
 // ---- Subsystem I ----------------------------------------------------------
@@ -903,7 +908,7 @@ void free_all(ecpic_ctx *c) {
         F(c->ek[b]); F(c->eyk[b]); F(c->ezk[b]);
     }
     F(c->wcnt); F(c->base); F(c->cbase); F(c->nstart); F(c->part);
-    F(c->E0y); F(c->E0z); F(c->taps1); F(c->dprev);
+    F(c->E0[0]); F(c->E0[1]); F(c->taps1); F(c->dprev);
     F(c->spart); F(c->epart);
     for (auto &t : c->tapsA_by_dt) F(t.second.dev);
     F(c->coefA); F(c->coefE[0]); F(c->coefE[1]); F(c->coefAk[0]); F(c->coefAk[1]);
@@ -975,7 +980,7 @@ int alloc_all(ecpic_ctx *c) {
     rc |= dalloc(&c->nstart, (size_t)2 * M + 1);
     // per item and wave: Subsystem I P+4 values, Subsystem II 2 (P+1)
     rc |= dalloc(&c->part, pn * (c->part_stride ? 3 : 1));
-    rc |= dalloc(&c->E0y, M); rc |= dalloc(&c->E0z, M);
+    rc |= dalloc(&c->E0[0], 2 * (size_t)M); rc |= dalloc(&c->E0[1], 2 * (size_t)M);
     const size_t nrec = (size_t)(M + 2);
     rc |= dalloc(&c->coefA, nrec * 2 * (c->P + 1));
     rc |= dalloc(&c->coefAk[0], nrec * 2 * (c->P + 1)); rc |= dalloc(&c->coefAk[1], nrec * 2 * (c->P + 1));

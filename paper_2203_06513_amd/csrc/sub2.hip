@@ -711,7 +711,8 @@ __global__ void __launch_bounds__(256) k_begin_step(DevStatus *stI, const DevSta
 // commit.  Each block forms the committed e_perp^{n+1} = e^(kc+1) and
 // a^{n+1} = a^n - dt/2 (e^n + e^{n+1}) on its whole window from the iterates
 // (one memory round trip, both parity candidates loaded), writes them on its
-// own cells, and does the step-start work of step n+1 from that window.
+// own cells, and does the step-start work of step n+1 from that window.  On a small grid
+// every block also reads E0 of step n on all cells; E0 of step n+1 goes elsewhere.
 struct JoinArgs {
     DevStatus *st;                         // Subsystem II status of step n
     const DevStatus *stI;                  // Subsystem I status of step n (mirrored)
