@@ -850,7 +850,8 @@ int substep_I(ecpic_ctx *c, double dt, ecpic_iter_stats *stats, bool adjoint, bo
         first_residuals_I(c, stats->residual_hist);
     }
     if (rc) {
-        c->have_prev = had_prev;   // no commit: the increments are those of before
+        // no commit: the increments are those of before (a commit that raised a flag wrote over them)
+        c->have_prev = had_prev && !c->h->I.committed;
         return rc;
     }
     guess = std::max(1, c->h->I.kconv + 1);
@@ -1526,12 +1527,12 @@ int finish_symmetric(ecpic_ctx *c, int sA, const StepSnap &q, int gI, int gII, i
     set_slot(c, sA);
     c->kI = gI;
     c->kII = gII;
-    bool again = false, turned = false, closing = false, committed = false;
+    bool again = false, turned = false, closing = false;
     c->dt = h;
     int rc = finish_I(c, &again);
+    const bool committed = c->h->I.committed;
     step_stats(c, &a, nullptr);
     if (!rc) {
-        committed = true;
         if (c->ws_prev) c->have_prev = true;
         c->guessI = std::max(1, c->h->I.kconv + 1);
         c->n_items_host = c->h->I.n_items_next;
@@ -1802,6 +1803,7 @@ int ecpic_step(ecpic_ctx *c, int32_t nsteps, ecpic_iter_stats *sI, ecpic_iter_st
             IIView v{c->pb[c->cur ^ 1].xi, c->pb[c->cur ^ 1].p, c->items[c->icur ^ 1], false, true, c->items[c->icur]};
             bool again = false;
             rc = finish_I(c, &again);
+            const bool committed = c->h->I.committed;   // and has written its increments
             if (!rc && again) {   // Subsystem I needed extra sweeps: run II now
                 c->kII = 0;
                 enqueue_spin_source(c, true);
@@ -1811,7 +1813,10 @@ int ecpic_step(ecpic_ctx *c, int32_t nsteps, ecpic_iter_stats *sI, ecpic_iter_st
             }
             if (!rc) rc = finish_II(c, v);
             step_stats(c, sI ? sI + done + j : nullptr, sII ? sII + done + j : nullptr);
-            if (rc) {   // nothing swapped: the step is rolled back
+            // rolled back (nothing swapped): the increments kept are those of before, or of
+            // an order undone
+            c->have_prev = rc ? snaps[j].have_prev && !committed : c->ws_prev;
+            if (rc) {
                 if (steps_done) *steps_done = done + j;
                 return rc;
             }
