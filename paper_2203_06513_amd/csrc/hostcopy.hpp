@@ -84,9 +84,10 @@ public:
         return (hipError_t)err.load();
     }
 
-    // A small array from pinned memory to dst.
-    static hipError_t from_pinned(void *dst, const void *src, size_t bytes) {
-        if (!pageable(dst)) return hipMemcpy(dst, src, bytes, hipMemcpyDefault);
+    // A small array from pinned memory to dst.  (Not a blocking copy where the runtime makes
+    // it: that one would wait for the work of other streams.)
+    static hipError_t from_pinned(void *dst, const void *src, size_t bytes, hipStream_t s) {
+        if (!pageable(dst)) return plain(dst, src, bytes, s, hipMemcpyDefault);
         std::memcpy(dst, src, bytes);
         return hipSuccess;
     }
@@ -95,8 +96,9 @@ private:
     static constexpr size_t SLOT = (size_t)2 << 20, MIN_PIECE = (size_t)512 << 10, MIN_BYTES = (size_t)3 << 20;
     static constexpr int SLOTS = 16, THREADS = 8;
 
-    static hipError_t plain(void *dst, const void *src, size_t bytes, hipStream_t s) {
-        const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
+    static hipError_t plain(void *dst, const void *src, size_t bytes, hipStream_t s,
+                            hipMemcpyKind kind = hipMemcpyDeviceToHost) {
+        const hipError_t e = hipMemcpyAsync(dst, src, bytes, kind, s);
         return e != hipSuccess ? e : hipStreamSynchronize(s);
     }
 

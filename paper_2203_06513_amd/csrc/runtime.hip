@@ -1294,7 +1294,8 @@ int ecpic_get_fields(ecpic_ctx *c, double *ex, double *ey, double *ez, double *a
         if (rc) return rc;
         for (int q = 0; q < 5; ++q)
             if (dst[q] &&
-                HostCopy::from_pinned(dst[q] + j0, c->h_fields + (size_t)q * n, sizeof(double) * n) != hipSuccess)
+                HostCopy::from_pinned(dst[q] + j0, c->h_fields + (size_t)q * n, sizeof(double) * n, c->stream) !=
+                    hipSuccess)
                 return ECPIC_EDEVICE;
     }
     return ECPIC_OK;

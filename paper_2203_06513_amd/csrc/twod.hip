@@ -3141,7 +3141,7 @@ int ecpic2d_get_fields(ecpic2d_ctx *c, double *e1, double *e2, double *bz, doubl
         const int rc = sync2(c);
         for (int q = 0; q < 5 && !rc; ++q)
             if (dst[q] && ecpic::HostCopy::from_pinned(dst[q], c->hfields + (size_t)q * c->Nc,
-                                                       sizeof(double) * c->Nc) != hipSuccess)
+                                                       sizeof(double) * c->Nc, c->stream) != hipSuccess)
                 return ECPIC_EDEVICE;
         return rc;
     }
