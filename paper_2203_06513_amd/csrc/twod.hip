@@ -25,12 +25,13 @@
 //
 // Linear solves.  Every linear operator of the 2D scheme is a sum of tensor
 // products of circulants (periodic B-spline mass matrices and differences), so
-// the 2D discrete Fourier transform diagonalises it: M1, M0 + dt^2 K/4 and the
-// Maxwell system are solved exactly by a forward transform, a division by the
-// symbol and an inverse transform.  The transforms are Stockham FFTs with the
-// values in registers (radix 8) and LDS between stages (rows in one kernel,
-// columns with the spectral step fused in the next, inverse rows with an
-// epilogue).
+// the 2D discrete Fourier transform diagonalises it: M0 + dt^2 K/4 and the Maxwell
+// system are solved exactly by a forward transform, a division by the symbol and an
+// inverse transform.  M1 is one tensor product a component, so its inverse is two 1D
+// circulant convolutions, with rows cut below 1e-18 of their largest entry.  The
+// transforms are Stockham FFTs with the values in registers (radix 8) and LDS between
+// stages (rows in one kernel, columns with the spectral step fused in the next, inverse
+// rows with an epilogue).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -45,6 +46,7 @@
 #include "coef.hpp"
 #include "common.hpp"
 #include "hostcopy.hpp"
+#include "inverse_row.hpp"
 #include "spline.hpp"
 
 namespace ecpic2d {
@@ -2036,8 +2038,8 @@ __global__ __launch_bounds__(SMALL_SOLVE / 8) void k2_solve_small(Ptrs<NB> src, 
 // ---- spectral steps -------------------------------------------------------
 // M1 is a tensor product on each component, so its inverse is one circulant
 // convolution along x2 and one along x1, with the first rows of the 1D inverses.
-// Those decay geometrically (99 entries above 1e-18 for the quadratic mass matrix, 133
-// for the cubic, about 240 for the quintic) and wrap around a grid that is shorter.
+// Those decay geometrically (down to 1e-18 in 101 entries for the quadratic mass matrix,
+// 135 for the cubic, 205 for the quintic) and wrap around a grid that is shorter.
 // A thread forms 8 neighbouring outputs from a sliding window: 64 FMAs per 8 LDS
 // reads, the weights in scalar registers.
 struct ConvTaps {           // one direction, per component
@@ -2954,33 +2956,11 @@ int ecpic2d_create(const ecpic2d_config *cfg, ecpic2d_ctx **out) {
     const int M1 = c->M1, M2 = c->M2;
     fill_dir(M1, dx1, &sy[0], &sy[M1], &sy[2 * M1], &sy[3 * M1]);
     fill_dir(M2, dx2, &sy[4 * M1], &sy[4 * M1 + M2], &sy[4 * M1 + 2 * M2], &sy[4 * M1 + 3 * M2]);
-    // First rows of the inverses of the 1D mass matrices, from their eigenvalues lam:
-    // c_m = (1/M) sum_k cos(2 pi k m / M) / lam_k, kept while above 1e-18 c_0 (the whole
-    // period if it is shorter).
-    auto inverse_row = [&](int M, const double *lam, std::vector<double> &row, int &hi) {
-        std::vector<long double> cs(M), inv(M);
-        for (int k = 0; k < M; ++k) {
-            cs[k] = cosl(2 * PI * k / M);
-            inv[k] = 1.0L / (long double)lam[k];
-        }
-        auto entry = [&](int m) {
-            long double v = 0;
-            for (int k = 0; k < M; ++k) v += inv[k] * cs[(int)(((int64_t)k * m) & (M - 1))];
-            return (double)(v / M);
-        };
-        std::vector<double> half(1, entry(0));
-        while ((int)half.size() < M / 2 && std::fabs(half.back()) > 1e-18 * half[0]) half.push_back(entry((int)half.size()));
-        const bool whole = (int)half.size() >= M / 2;
-        const int lo = whole ? M / 2 - 1 : (int)half.size() - 1;   // offsets -lo .. hi
-        hi = whole ? M / 2 : lo;
-        if (whole) half.resize(M / 2), half.push_back(entry(M / 2));
-        row.assign(lo + hi + 1, 0.0);
-        for (int m = -lo; m <= hi; ++m) row[hi - m] = half[std::abs(m)];   // reversed: first the largest offset
-    };
-    auto conv_taps = [&](int M, const double *m0, const double *m1, bool first_is_m1, ConvTaps &t) {
+    // rows of M1^{-1}: component 1 is m1(x1) m0(x2), component 2 m0(x1) m1(x2)
+    auto conv_taps = [&](int M, double dx, bool first_is_m1, ConvTaps &t) {
         for (int b = 0; b < 2; ++b) {
-            std::vector<double> row;
-            inverse_row(M, (b == 0) == first_is_m1 ? m1 : m0, row, t.hi[b]);
+            const std::vector<double> row =
+                inverse_row(M, (b == 0) == first_is_m1 ? c->m1row : c->m0row, dx, t.hi[b]);
             t.nt[b] = (int)row.size();
             std::vector<double> pad(8 + conv_steps(t.nt[b]) + 16, 0.0);
             std::copy(row.begin(), row.end(), pad.begin() + 8);
@@ -2992,9 +2972,7 @@ int ecpic2d_create(const ecpic2d_config *cfg, ecpic2d_ctx **out) {
         }
         return true;
     };
-    // component 1: m1(x1) m0(x2), component 2: m0(x1) m1(x2)
-    bool ok = conv_taps(M1, &sy[0], &sy[M1], true, c->conv_a) &&
-              conv_taps(M2, &sy[4 * M1], &sy[4 * M1 + M2], false, c->conv_b);
+    bool ok = conv_taps(M1, dx1, true, c->conv_a) && conv_taps(M2, dx2, false, c->conv_b);
     ok = ok && hipMemcpy(c->tw1, t1.data(), sizeof(double2) * t1.size(), hipMemcpyHostToDevice) == hipSuccess &&
               hipMemcpy(c->tw2, t2.data(), sizeof(double2) * t2.size(), hipMemcpyHostToDevice) == hipSuccess &&
               hipMemcpy(c->sym, sy.data(), sizeof(double) * sy.size(), hipMemcpyHostToDevice) == hipSuccess;
