@@ -10,6 +10,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <sched.h>
 
 #include <algorithm>
 #include <atomic>
@@ -39,7 +40,7 @@ public:
         if (bytes < MIN_BYTES || !pageable(dst) || !ready()) return plain(dst, src, bytes, s);
         const size_t piece = std::min(SLOT, std::max(MIN_PIECE, bytes / 16 / MIN_PIECE * MIN_PIECE));
         const size_t chunks = (bytes + piece - 1) / piece;
-        const int threads = (int)std::min<size_t>(THREADS, chunks / 2);
+        const int threads = (int)std::min<size_t>(std::min(THREADS, processors()), chunks / 2);
         auto size_of = [&](size_t k) { return std::min(piece, bytes - k * piece); };
         // Thread t moves the chunks k = t mod threads.  filled counts the chunks whose
         // DMA is queued (its event recorded), moved[slot] those a slot has passed on.
@@ -100,6 +101,12 @@ private:
                             hipMemcpyKind kind = hipMemcpyDeviceToHost) {
         const hipError_t e = hipMemcpyAsync(dst, src, bytes, kind, s);
         return e != hipSuccess ? e : hipStreamSynchronize(s);
+    }
+
+    // Processors the calling thread may run on (the threads it starts inherit them).
+    static int processors() {
+        cpu_set_t set;
+        return sched_getaffinity(0, sizeof(set), &set) == 0 ? std::max(1, CPU_COUNT(&set)) : THREADS;
     }
 
     // Memory the runtime knows (pinned by the caller, or on a device) needs no ring.
