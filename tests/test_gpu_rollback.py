@@ -66,3 +66,57 @@ def test_failed_first_step_leaves_no_previous_start(splitting, M):
     assert out[0][0] == out[1][0]
     for k in out[0][1]:
         np.testing.assert_array_equal(out[0][1][k], out[1][1][k])
+
+
+# (splitting, spin, M, dt, sigma, amplitude, hbar, tol, allowed sweeps, what fails): runs whose
+# need grows past the allowed sweeps at some step, in the oracle's counts at steps 4, 12, 0; 3,
+# 15, 0 (closing substep alone); 9, 10, 2 (plain steps: Subsystem I; II); 10, 15, 17 (with spin)
+GROWING = [
+    (1, False, 32, 0.1, 0.08, 0.0, 0.0, 1e-12, 4, "closing"),
+    (1, False, 160, 0.05, 0.3, 0.0, 0.0, 1e-13, 4, "closing"),
+    (1, False, 160, 0.1, 0.08, 0.0, 0.0, 3e-12, 4, "closing"),
+    (1, True, 32, 0.1, 0.15, 0.0, 1e-5, 1e-12, 4, "closing"),
+    (1, True, 160, 0.05, 0.3, 0.0, 1e-5, 1e-13, 4, "closing"),
+    (1, True, 160, 0.1, 0.08, 0.0, 1e-5, 3e-12, 4, "closing"),
+    (0, False, 32, 0.05, 0.08, 0.0, 0.0, 1e-12, 4, "I"),
+    (0, False, 160, 0.05, 0.3, 0.0, 0.0, 1e-11, 4, "I"),
+    (0, False, 32, 0.1, 0.3, 0.3, 0.0, 3e-12, 5, "II"),
+    (0, True, 32, 0.05, 0.08, 0.0, 1e-5, 1e-12, 4, "I"),
+    (0, True, 160, 0.05, 0.3, 0.0, 1e-5, 1e-11, 4, "I"),
+    (0, True, 32, 0.1, 0.3, 0.3, 1e-2, 3e-12, 5, "II"),
+]
+
+
+@pytest.mark.parametrize("guess", [0, 1])   # the default, and too few sweeps queued at first
+@pytest.mark.parametrize("splitting,spin,M,dt,sigma,amplitude,hbar,tol,allowed,what", GROWING)
+def test_failing_step_leaves_the_step_before(splitting, spin, M, dt, sigma, amplitude, hbar, tol, allowed, what,
+                                             guess):
+    """The steps before a failing one stand and its own start is put back, bit for bit (e_x and
+    the item list too, which the closing adjoint substep writes over), and what is run
+    from there is what a context that took only those steps runs."""
+    steps = 24
+    w = workloads.get("paper52" if spin else "paper51").scaled(
+        M=M, L=0.25 * M, n_particles=2000, dt=dt, sigma=sigma, amplitude=amplitude, hbar=hbar, tol=tol)
+    arr = workloads.generate(w)
+    kw = dict(map=ec.MAP_SEIDEL, splitting=splitting, sweep_guess=guess)
+    with ec.Context.from_workload(w, **kw) as c:
+        c.load(arr)
+        _, _, kI, kII, _ = c.step(steps)
+        need = dict(I=kI, II=kII, closing=c.last_sweeps_I2)
+    over = {k: np.flatnonzero(v > allowed) for k, v in need.items()}
+    j = min(v[0] for v in over.values() if len(v))
+    assert [k for k, v in over.items() if len(v) and v[0] == j] == [what]
+    out = []
+    for fail in (True, False):
+        with ec.Context.from_workload(w, **dict(kw, **(dict(max_iter=allowed) if fail else {}))) as c:
+            c.load(arr)
+            rc, done, *_ = c.step(steps if fail else int(j), check=False)
+            assert rc == (ec.ENOTCONV if fail else 0) and done == j
+            states = [c.state()]
+            c.substep_particles(0.1 * dt)
+            c.substep_fields(0.1 * dt)
+            c.substep_particles_adjoint(0.1 * dt)
+            out.append(states + [c.state()])
+    for a, b in zip(*out):
+        for k in a:
+            np.testing.assert_array_equal(a[k], b[k], err_msg=k)
