@@ -2,7 +2,6 @@
 #pragma once
 
 #include <cmath>
-#include <cstdint>
 #include <cstdlib>
 #include <vector>
 
@@ -18,16 +17,17 @@ namespace ecpic2d {
 inline std::vector<double> inverse_row(int M, const std::vector<double> &mass, double dx, int &hi) {
     const long double PI = 3.14159265358979323846264338327950288L;
     const int d = (int)mass.size() / 2;
-    std::vector<long double> cs(M), inv(M);
-    for (int k = 0; k < M; ++k) cs[k] = cosl(2 * PI * k / M);
-    for (int k = 0; k < M; ++k) {
+    // eigenvalues and cosines are even in k: half of them, the inner ones twice
+    std::vector<long double> cs(M), inv(M / 2 + 1);
+    for (int k = 0; k <= M / 2; ++k) cs[k] = cs[(M - k) & (M - 1)] = cosl(2 * PI * k / M);
+    for (int k = 0; k <= M / 2; ++k) {
         long double lam = mass[d];
-        for (int q = 1; q <= d; ++q) lam += 2 * (long double)mass[d + q] * cs[(int)(((int64_t)k * q) & (M - 1))];
-        inv[k] = 1.0L / (lam * dx);
+        for (int q = 1; q <= d; ++q) lam += 2 * (long double)mass[d + q] * cs[(k * q) & (M - 1)];
+        inv[k] = (k == 0 || k == M / 2 ? 1.0L : 2.0L) / (lam * dx);
     }
     auto entry = [&](int m) {
         long double v = 0;
-        for (int k = 0; k < M; ++k) v += inv[k] * cs[(int)(((int64_t)k * m) & (M - 1))];
+        for (int k = 0, i = 0; k <= M / 2; ++k, i = (i + m) & (M - 1)) v += inv[k] * cs[i];
         return (double)(v / M);
     };
     std::vector<double> half(1, entry(0));

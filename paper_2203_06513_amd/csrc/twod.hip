@@ -2922,10 +2922,9 @@ int ecpic2d_create(const ecpic2d_config *cfg, ecpic2d_ctx **out) {
         for (int b = 0; b < 2; ++b) rc |= dalloc(c, &c->sx[b], N) | dalloc(c, &c->sy[b], N) | dalloc(c, &c->sz[b], N);
         rc |= dalloc(c, &c->Dx, Nc) | dalloc(c, &c->Dy, Nc) | dalloc(c, &c->Dz, Nc) | dalloc(c, &c->ssrc, Nc);
     }
-    rc |= dalloc(c, &c->Z, 4 * Nc) | dalloc(c, &c->R, Nc) | dalloc(c, &c->tw1, (size_t)c->M1 / 2) |
-          dalloc(c, &c->tw2, (size_t)c->M2 / 2) | dalloc(c, &c->sym, 4 * (size_t)(c->M1 + c->M2)) |
-          dalloc(c, &c->partial, RED_BLOCKS + 16) | dalloc(c, &c->res, 3 * MAXK + 4) | dalloc(c, &c->flags, 1) |
-          dalloc(c, &c->gate, 2) | dalloc(c, &c->done, 1);
+    rc |= dalloc(c, &c->Z, 4 * Nc) | dalloc(c, &c->R, Nc) | dalloc(c, &c->partial, RED_BLOCKS + 16) |
+          dalloc(c, &c->res, 3 * MAXK + 4) | dalloc(c, &c->flags, 1) | dalloc(c, &c->gate, 2) |
+          dalloc(c, &c->done, 1);
     const size_t pinned = 2 * MAXK + (Nc <= (size_t)FIELDS_NODES ? 5 * Nc : 0);   // the mirror, then the fields
     if (rc || hipHostMalloc((void **)&c->hres, sizeof(double) * pinned, hipHostMallocMapped) != hipSuccess) {
         ecpic2d_destroy(c);
@@ -2963,27 +2962,34 @@ int ecpic2d_create(const ecpic2d_config *cfg, ecpic2d_ctx **out) {
     const int M1 = c->M1, M2 = c->M2;
     fill_dir(M1, dx1, &sy[0], &sy[M1], &sy[2 * M1], &sy[3 * M1]);
     fill_dir(M2, dx2, &sy[4 * M1], &sy[4 * M1 + M2], &sy[4 * M1 + 2 * M2], &sy[4 * M1 + 3 * M2]);
-    // rows of M1^{-1}: component 1 is m1(x1) m0(x2), component 2 m0(x1) m1(x2)
-    auto conv_taps = [&](int M, double dx, bool first_is_m1, ConvTaps &t) {
-        for (int b = 0; b < 2; ++b) {
-            const std::vector<double> row =
-                inverse_row(M, (b == 0) == first_is_m1 ? c->m1row : c->m0row, dx, t.hi[b]);
-            t.nt[b] = (int)row.size();
-            std::vector<double> pad(8 + conv_steps(t.nt[b]) + 16, 0.0);
-            std::copy(row.begin(), row.end(), pad.begin() + 8);
-            double *d = nullptr;
-            if (dalloc(c, &d, pad.size()) ||
-                hipMemcpy(d, pad.data(), sizeof(double) * pad.size(), hipMemcpyHostToDevice) != hipSuccess)
-                return false;
-            t.rt[b] = d + 8;
-        }
-        return true;
+    // The twiddles, the symbols and the rows of M1^{-1} (component 1: m1(x1) m0(x2),
+    // component 2: m0(x1) m1(x2)) go up in one block.
+    std::vector<double> tab;
+    auto append = [&](const double *v, size_t n) {
+        tab.insert(tab.end(), v, v + n);
+        return tab.size() - n;
     };
-    bool ok = conv_taps(M1, dx1, true, c->conv_a) && conv_taps(M2, dx2, false, c->conv_b);
-    ok = ok && hipMemcpy(c->tw1, t1.data(), sizeof(double2) * t1.size(), hipMemcpyHostToDevice) == hipSuccess &&
-              hipMemcpy(c->tw2, t2.data(), sizeof(double2) * t2.size(), hipMemcpyHostToDevice) == hipSuccess &&
-              hipMemcpy(c->sym, sy.data(), sizeof(double) * sy.size(), hipMemcpyHostToDevice) == hipSuccess;
-    if (!ok) { ecpic2d_destroy(c); return ECPIC_EDEVICE; }
+    const size_t at1 = append(&t1[0].x, M1), at2 = append(&t2[0].x, M2), at_sym = append(sy.data(), sy.size());
+    size_t at_row[4];
+    for (int q = 0; q < 4; ++q) {   // the rows along x1, then along x2
+        ConvTaps &t = q < 2 ? c->conv_a : c->conv_b;
+        const int b = q & 1;
+        const std::vector<double> row =
+            inverse_row(q < 2 ? M1 : M2, (b == 0) == (q < 2) ? c->m1row : c->m0row, q < 2 ? dx1 : dx2, t.hi[b]);
+        t.nt[b] = (int)row.size();
+        std::vector<double> pad(8 + conv_steps(t.nt[b]) + 16, 0.0);
+        std::copy(row.begin(), row.end(), pad.begin() + 8);
+        at_row[q] = append(pad.data(), pad.size()) + 8;
+    }
+    double *d = nullptr;
+    rc = dalloc(c, &d, tab.size());
+    if (!rc && hipMemcpy(d, tab.data(), sizeof(double) * tab.size(), hipMemcpyHostToDevice) != hipSuccess)
+        rc = ECPIC_EDEVICE;
+    if (rc) { ecpic2d_destroy(c); return rc; }
+    c->tw1 = reinterpret_cast<double2 *>(d + at1);
+    c->tw2 = reinterpret_cast<double2 *>(d + at2);
+    c->sym = d + at_sym;
+    for (int q = 0; q < 4; ++q) (q < 2 ? c->conv_a : c->conv_b).rt[q & 1] = d + at_row[q];
     for (double **gp : grids) k2_fill<<<grid_for(c->Nc), BLOCK, 0, c->stream>>>(*gp, c->Nc, 0.0);
     k2_fill_i32<<<grid_for(c->Nc), BLOCK, 0, c->stream>>>(c->count, c->Nc);
     // the commit accumulates arrivals per tile: every tile counter starts at zero
