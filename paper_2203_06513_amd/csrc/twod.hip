@@ -2150,8 +2150,8 @@ __global__ __launch_bounds__(BLOCK) void k2_conv_cols(const double *__restrict__
 }
 
 // Both directions in one block per component, for grids of at most CONV_SMALL nodes
-// (two FFT solves took 15.7 us at 16 x 16 nodes, this takes 10; 64 x 64 in 20 us, the
-// two kernels above 27 us at 128 x 128; 512 x 512: 35 us, by FFTs 48).
+// (two FFT solves took 15.7 us at 16 x 16 nodes, this takes 8.6; 64 x 64 in 18 us, the
+// two kernels above 23 us at 128 x 128; 512 x 512: 34 us, by FFTs 48).
 constexpr int CONV_SMALL = 4096;
 
 template <class Epi>
