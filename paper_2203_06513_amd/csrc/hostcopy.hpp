@@ -112,8 +112,9 @@ private:
     // Memory the runtime knows (pinned by the caller, or on a device) needs no ring.
     static bool pageable(const void *dst) {
         hipPointerAttribute_t at{};
+        const bool clean = hipPeekAtLastError() == hipSuccess;   // else the error is a launch's, and stays
         if (hipPointerGetAttributes(&at, dst) != hipSuccess) {
-            (void)hipGetLastError();
+            if (clean) (void)hipGetLastError();
             return dst != nullptr;
         }
         return dst && at.type == hipMemoryTypeUnregistered;

@@ -2628,7 +2628,10 @@ int wait_mirror(ecpic2d_ctx *c, const double *h, double &r) {
         if (n % 32 == 0) std::this_thread::yield();
         else __builtin_ia32_pause();
         if (n % 4096 == 0) {
-            const hipError_t e = hipStreamQuery(c->stream);
+            // an error that a launch has left for the end of the call is not queried over
+            const hipError_t left = hipPeekAtLastError();
+            const bool query = left == hipSuccess || left == hipErrorNotReady;
+            const hipError_t e = query ? hipStreamQuery(c->stream) : hipStreamSynchronize(c->stream);
             if (hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();   // no error
             if (e == hipErrorNotReady) continue;
             if (e != hipSuccess || *flag == MIRROR_WAIT) return ECPIC_EDEVICE;
